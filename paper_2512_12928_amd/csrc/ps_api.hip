@@ -1,6 +1,10 @@
 // Host side of the C ABI declared in include/ps.h: argument validation, work-list
 // construction, metadata staging, kernel launches, swap tickets.
+#include <sched.h>
+
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -38,9 +42,15 @@ constexpr int kMaxSwap = 16384;   // blocks per swap call
 constexpr int kTicketRing = 64;
 constexpr int kStagingBlocks = 1024;  // blocks a swap staging buffer holds (64 MiB at 64 KiB per block)
 
+// A pinned staging buffer.  A step's slot is given back by a kernel of that step: its attention launch, which starts once
+// the prologue (the slot's only reader) is over, writes the slot's current use number into `word`.  An event recorded
+// behind the prologue for the same purpose put about 5 us between the two kernels, and a second one at the end of the step
+// as much in front of the next step.  Swap slots are given back by the event of the call's ticket (`ev`, not owned here).
 struct StageSlot {
   void* pinned = nullptr;
   size_t cap = 0;
+  volatile uint32_t* word = nullptr;  // pinned; use number of the last step whose slot reads are over
+  uint32_t use = 0;                   // number of the slot's current use
   hipEvent_t ev = nullptr;
   bool in_flight = false;
 };
@@ -60,7 +70,7 @@ constexpr int kMaxDevices = 64;
 struct StaticScratch {
   unsigned char* ptr = nullptr;   // device address of `scratch` on this GPU (hipGetSymbolAddress)
   int next = 0;                   // which of the two description copies the next call takes
-  hipEvent_t done[2] = {nullptr, nullptr};
+  hipEvent_t done = nullptr;      // see order_streams
   hipStream_t last_stream[2] = {nullptr, nullptr};
   bool used[2] = {false, false};
 };
@@ -80,6 +90,7 @@ struct ps_ctx {
   size_t block_bytes = 0;
   float scale_log2 = 0.f;
   StageSlot step_slot[kStepSlots];
+  uint32_t* slot_words = nullptr;  // pinned, one cache line per step slot
   int step_next = 0;
   StageSlot swap_slot[kSwapSlots];
   int swap_next = 0;
@@ -92,8 +103,8 @@ struct ps_ctx {
     char* dev = nullptr;
     size_t cap = 0;
     hipEvent_t uploaded = nullptr;  // on the copy stream, after the upload
-    hipEvent_t done = nullptr;      // on the launching stream, after the last kernel that reads it
-    hipStream_t last_stream = nullptr;  // the stream `done` was last recorded on
+    hipEvent_t done = nullptr;      // see order_streams; with own_streams: after the last kernel that reads the buffer
+    hipStream_t last_stream = nullptr;  // the stream of the last kernels that read the buffer
     bool used = false;
   } meta[2];
   int meta_next = 0;
@@ -524,11 +535,52 @@ MetaLayout meta_layout(int n_req, size_t n_aitems, int64_t n_table, size_t n_dit
 
 constexpr int kMinChunk = 32;
 
-int acquire_slot(StageSlot& s, size_t bytes) {
-  if (s.in_flight) {
+// Waits until the GPU no longer reads the slot.  A step slot's word is polled (its step is kStepSlots steps back: when the
+// host runs that far ahead it has time); the two-second limit only matters if the launch that writes the word never ran.
+int release_slot(StageSlot& s) {
+  if (!s.in_flight) return PS_OK;
+  if (s.word) {
+    const auto begin = std::chrono::steady_clock::now();
+    for (uint32_t spins = 1; (int32_t)(*s.word - s.use) < 0; ++spins) {
+      if (spins % 64 == 0) {
+        sched_yield();
+        if (std::chrono::steady_clock::now() - begin > std::chrono::seconds(2)) {
+          PS_HIP(hipDeviceSynchronize());
+          break;
+        }
+      }
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+  } else {
     PS_HIP(hipEventSynchronize(s.ev));
-    s.in_flight = false;
   }
+  s.in_flight = false;
+  return PS_OK;
+}
+
+// Everything enqueued on `later` from now on runs after everything enqueued on `earlier` so far.  Called when a buffer
+// changes from one stream to another: the event is recorded then, not at the end of every step, because recording one
+// costs a stream about 5 us and steps of one context almost always share a stream.
+int order_streams(hipStream_t earlier, hipStream_t later, hipEvent_t ev) {
+  if (hipEventRecord(ev, earlier) != hipSuccess) {  // that stream is gone: whatever it still ran has to be over
+    (void)hipGetLastError();
+    PS_HIP(hipDeviceSynchronize());
+    return PS_OK;
+  }
+  PS_HIP(hipStreamWaitEvent(later, ev, 0));
+  return PS_OK;
+}
+
+// Whether work enqueued on the stream now is recorded into a graph instead of run.
+bool is_capturing(hipStream_t s) {
+  if (s == nullptr) return false;  // the default stream cannot be captured
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
+int acquire_slot(StageSlot& s, size_t bytes) {
+  int rc = release_slot(s);
+  if (rc != PS_OK) return rc;
   if (s.cap < bytes) {
     if (s.pinned) PS_HIP(hipHostFree(s.pinned));
     s.pinned = nullptr;
@@ -614,14 +666,17 @@ int ps_create(const ps_layer_cfg* cfg, ps_ctx** out) {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->n_cus, hipDeviceAttributeMultiprocessorCount, c->device);
   if (e == hipSuccess && c->n_cus < 1) c->n_cus = 1;
   for (int i = 0; i < kStepSlots && e == hipSuccess; ++i) {
-    e = hipEventCreateWithFlags(&c->step_slot[i].ev, hipEventDisableTiming);
     // staging for the batch description, large enough for every batch ps_step_static accepts, so that a step
     // only allocates when a batch is larger than that
-    if (e == hipSuccess) e = hipHostMalloc(&c->step_slot[i].pinned, kStepStaging, hipHostMallocDefault);
+    e = hipHostMalloc(&c->step_slot[i].pinned, kStepStaging, hipHostMallocDefault);
     if (e == hipSuccess) c->step_slot[i].cap = kStepStaging;
   }
-  for (int i = 0; i < kSwapSlots && e == hipSuccess; ++i)
-    e = hipEventCreateWithFlags(&c->swap_slot[i].ev, hipEventDisableTiming);
+  constexpr size_t kWordStride = 64 / sizeof(uint32_t);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&c->slot_words, kStepSlots * 64, hipHostMallocDefault);
+  if (e == hipSuccess) {
+    std::memset(c->slot_words, 0, kStepSlots * 64);
+    for (int i = 0; i < kStepSlots; ++i) c->step_slot[i].word = c->slot_words + i * kWordStride;
+  }
   for (int i = 0; i < kTicketRing && e == hipSuccess; ++i)
     e = hipEventCreateWithFlags(&c->ticket_ev[i], hipEventDisableTiming);
   for (int i = 0; i < 6 && e == hipSuccess; ++i) e = hipEventCreate(&c->prof_ring[0][i]);
@@ -652,14 +707,11 @@ int ps_create(const ps_layer_cfg* cfg, ps_ctx** out) {
 void ps_destroy(ps_ctx* c) {
   if (!c) return;
   (void)hipDeviceSynchronize();
-  for (auto& s : c->step_slot) {
+  for (auto& s : c->step_slot)
     if (s.pinned) (void)hipHostFree(s.pinned);
-    if (s.ev) (void)hipEventDestroy(s.ev);
-  }
-  for (auto& s : c->swap_slot) {
+  if (c->slot_words) (void)hipHostFree(c->slot_words);
+  for (auto& s : c->swap_slot)
     if (s.pinned) (void)hipHostFree(s.pinned);
-    if (s.ev) (void)hipEventDestroy(s.ev);
-  }
   for (auto& e : c->ticket_ev)
     if (e) (void)hipEventDestroy(e);
   for (auto& slot_ev : c->prof_ring)
@@ -990,12 +1042,20 @@ static int launch_phases(ps_ctx* c, const char* h, size_t upload_bytes, const ps
   P.G = c->G;
   P.out_f32 = c->cfg.out_dtype == PS_F32;
   P.scale_log2 = c->scale_log2;
+  // the attention launch hands the pinned slot back (a step that is being captured runs later, any number of times:
+  // its slot is not handed back by it)
+  const bool hand_back = h && !is_capturing(stream);
+  if (hand_back) {
+    slot.use += 1;
+    slot.in_flight = true;
+  }
+  P.slot_word = hand_back ? (uint32_t*)slot.word : nullptr;
+  P.slot_use = slot.use;
 
   // Prologue: one launch.  It appends the new K/V rows and, unless the context's copy stream has
   // already brought the batch description over, uploads it with a kernel that reads the pinned slot
   // over the host link (a third of the latency of a DMA copy).
   PS_HIP(ps::launch_prologue(P, h, w, upload_bytes, aitems_src, k_new ? (int)c->aitems.size() : 0, stream));
-  if (h && (upload_bytes > 0 || k_new)) PS_HIP(hipEventRecord(slot.ev, stream));  // last reader of the pinned slot
   if (prof) PS_HIP(hipEventRecord(c->prof_ev_now()[2], stream));
   // Attention: one launch for the decode slots and the prefill tiles (decode streams the cache at
   // HBM speed and leaves the matrix pipes idle, prefill is the opposite: they run side by side on
@@ -1025,15 +1085,13 @@ static int launch_phases(ps_ctx* c, const char* h, size_t upload_bytes, const ps
     c->prof_valid = true;
     c->prof_mode = prof;
   }
-  // whoever writes this copy of the batch description next (two steps on, maybe from another stream) waits for this
+  // whoever writes this copy of the batch description next (two steps on, maybe from another stream) runs after this
   if (c->last.mb) {
-    PS_HIP(hipEventRecord(c->last.mb->done, stream));
+    if (c->copy) PS_HIP(hipEventRecord(c->last.mb->done, stream));
     c->last.mb->last_stream = stream;
   } else {
     StaticScratch& ss = g_static[c->device];
-    const int which = w == (char*)ss.ptr ? 0 : 1;
-    PS_HIP(hipEventRecord(ss.done[which], stream));
-    ss.last_stream[which] = stream;
+    ss.last_stream[w == (char*)ss.ptr ? 0 : 1] = stream;
   }
   return PS_OK;
 }
@@ -1049,7 +1107,7 @@ static int static_scratch(ps_ctx* c, StaticScratch** out) {
     void* p = nullptr;
     PS_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
     if (!p) return fail(PS_EHIP, "hipGetSymbolAddress returned NULL");
-    for (int i = 0; i < 2; ++i) PS_HIP(hipEventCreateWithFlags(&ss.done[i], hipEventDisableTiming));
+    PS_HIP(hipEventCreateWithFlags(&ss.done, hipEventDisableTiming));
     ss.ptr = (unsigned char*)p;
   }
   *out = &ss;
@@ -1141,13 +1199,15 @@ static int step_impl(ps_ctx* c, const ps_batch* b, const void* q, const void* k_
     const int which = ss->next;
     ss->next ^= 1;
     if (wait_ev) PS_HIP(hipStreamWaitEvent(stream, wait_ev, 0));
-    if (ss->used[which] && ss->last_stream[which] != stream) PS_HIP(hipStreamWaitEvent(stream, ss->done[which], 0));
+    if (ss->used[which] && ss->last_stream[which] != stream) {
+      rc = order_streams(ss->last_stream[which], stream, ss->done);
+      if (rc != PS_OK) return rc;
+    }
     ss->used[which] = true;
     if (prof) {
       PS_HIP(hipEventRecord(c->prof_ev_now()[0], stream));
       PS_HIP(hipEventRecord(c->prof_ev_now()[1], stream));
     }
-    slot.in_flight = true;
     c->last.valid = false;
     c->last.meta_dev = (char*)ss->ptr + (size_t)which * kStaticMeta;
     c->last.mb = nullptr;
@@ -1177,7 +1237,6 @@ static int step_impl(ps_ctx* c, const ps_batch* b, const void* q, const void* k_
   if (c->copy) {  // own copy stream: the upload does not wait for the caller's earlier work
     if (mb.used) PS_HIP(hipStreamWaitEvent(c->copy, mb.done, 0));
     PS_HIP(hipMemcpyAsync(mb.dev, h, ml.total, hipMemcpyHostToDevice, c->copy));
-    PS_HIP(hipEventRecord(slot.ev, c->copy));
     PS_HIP(hipEventRecord(mb.uploaded, c->copy));
     if (wait_ev) PS_HIP(hipStreamWaitEvent(stream, wait_ev, 0));
     if (prof) PS_HIP(hipEventRecord(c->prof_ev_now()[0], stream));
@@ -1186,11 +1245,13 @@ static int step_impl(ps_ctx* c, const ps_batch* b, const void* q, const void* k_
     if (wait_ev) PS_HIP(hipStreamWaitEvent(stream, wait_ev, 0));
     // the step before last read this copy of the description; on the same stream it is over by order, on another
     // stream this one waits for it before the prologue overwrites the lists
-    if (mb.used && mb.last_stream != stream) PS_HIP(hipStreamWaitEvent(stream, mb.done, 0));
+    if (mb.used && mb.last_stream != stream) {
+      rc = order_streams(mb.last_stream, stream, mb.done);
+      if (rc != PS_OK) return rc;
+    }
     if (prof) PS_HIP(hipEventRecord(c->prof_ev_now()[0], stream));
     // the upload is part of the prologue kernel launched below
   }
-  slot.in_flight = true;
   mb.used = true;
   if (prof) PS_HIP(hipEventRecord(c->prof_ev_now()[1], stream));
   c->last.valid = false;
@@ -1246,7 +1307,14 @@ int ps_step_next_layer(ps_ctx* c, const void* q, const void* k_new, const void* 
   // the append items are taken from the device copy of the batch description this time
   const char* w = c->last.meta_dev;
   // a call on another stream than the one the batch was uploaded on: ordered by the caller (see ps.h), but the wait is cheap
-  if (c->last.mb && c->last.mb->last_stream != stream) PS_HIP(hipStreamWaitEvent(stream, c->last.mb->done, 0));
+  if (c->last.mb && c->last.mb->last_stream != stream) {
+    if (c->copy) {
+      PS_HIP(hipStreamWaitEvent(stream, c->last.mb->done, 0));
+    } else {
+      int rc = order_streams(c->last.mb->last_stream, stream, c->last.mb->done);
+      if (rc != PS_OK) return rc;
+    }
+  }
   return launch_phases(c, nullptr, 0, (const ps::AppendItem*)(w + c->last.off[4]), q, k_new, v_new, kv_cache, out, workspace,
                        stream);
 }
@@ -1317,7 +1385,6 @@ static int swap_common(ps_ctx* c, bool out_dir, const int32_t* dev_ids, const in
   hipStream_t stream = (hipStream_t)side_stream;
 
   const int si = c->swap_next;
-  (void)si;
   c->swap_next = (c->swap_next + 1) % kSwapSlots;
   StageSlot& slot = c->swap_slot[si];
   int rc = acquire_slot(slot, (size_t)3 * kMaxSwap * sizeof(int32_t));
@@ -1369,14 +1436,15 @@ static int swap_common(ps_ctx* c, bool out_dir, const int32_t* dev_ids, const in
     else
       PS_HIP(ps::launch_block_copy(d + m, d, m, host_pool, const_cast<void*>(kv_cache), c->block_bytes, wgs, stream));
   }
-  PS_HIP(hipEventRecord(slot.ev, stream));
-  slot.in_flight = true;
-
+  // the call's event: its ticket, and the end of the id list's use (a swap slot is used again long before the event is)
   const uint64_t id = c->next_ticket++;
   const int ts = (int)(id % kTicketRing);
+  static_assert(kSwapSlots < kTicketRing, "a swap slot's event is still its own when the slot comes round again");
   if (c->ticket_id[ts] != 0) PS_HIP(hipEventSynchronize(c->ticket_ev[ts]));  // recycled: older copy must be over
   PS_HIP(hipEventRecord(c->ticket_ev[ts], stream));
   c->ticket_id[ts] = id;
+  slot.ev = c->ticket_ev[ts];
+  slot.in_flight = true;
   *n_done = m;
   *ticket = id;
   return PS_OK;

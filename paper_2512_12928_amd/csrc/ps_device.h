@@ -64,6 +64,13 @@ __device__ __forceinline__ void clock_record(const StepParams& P, int slot, int 
   }
 }
 
+// The first thread of an attention launch hands the step's pinned staging slot back to the host: the launch started after
+// the prologue, the slot's only reader, had ended.
+__device__ __forceinline__ void hand_back_slot(const StepParams& P) {
+  if (P.slot_word != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
+    __hip_atomic_store(P.slot_word, P.slot_use, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ __forceinline__ bf16x8 load_stream16(const uint16_t* p) {
   return __builtin_bit_cast(bf16x8, __builtin_nontemporal_load((const u32x4*)p));
 }

@@ -111,6 +111,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(3
       P.clocks[bid * 4 + 1] = __builtin_amdgcn_s_memrealtime();
     }
   }
+  hand_back_slot(P);
   if (threadIdx.x < kFusedRing) {
     sm.ready[threadIdx.x] = 0;
     sm.consumed[threadIdx.x] = 0;

@@ -76,6 +76,9 @@ struct StepParams {
   int32_t Hq, Hkv, G;
   int32_t out_f32;
   float scale_log2;  // softmax_scale * log2(e)
+  uint32_t slot_use;     // what slot_word is set to
+  uint32_t* slot_word;   // pinned host word: the attention launch says here that the prologue's reads of the pinned
+                         // staging slot are over; NULL: nobody waits for it
 };
 
 // Launchers (ps_kernels.hip). Each checks its own launch and returns the hipError_t.

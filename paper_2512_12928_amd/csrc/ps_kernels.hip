@@ -669,6 +669,7 @@ __global__ __launch_bounds__(kPrefillWaves * 64) void attention_kernel(StepParam
                                                                        int n_decode_wgs, int HW, int n_zsplit) {
   __shared__ __attribute__((aligned(16))) char lds[sizeof(PrefillStage) * kStages + kIdTiles * 4 * sizeof(int)];
   static_assert(sizeof(DecodeQ) * kDecodeWaves <= sizeof(PrefillStage) * kStages, "decode Q copies fit the prefill ring");
+  hand_back_slot(P);
   {
     const int role_idx = (int)blockIdx.x < n_decode_wgs ? (int)blockIdx.x : (int)blockIdx.x - n_decode_wgs;
     if (role_idx < kClockSlots) clock_record(P, ((int)blockIdx.x < n_decode_wgs ? 0 : kClockSlots) + role_idx, 0);

@@ -68,6 +68,9 @@ class ps_trace_req(C.Structure):
                 ("out_len", C.c_int32), ("reserved", C.c_int32)]
 
 
+_TRACE_DTYPE = np.dtype(ps_trace_req)   # the same layout
+
+
 class ps_sim_result(C.Structure):
     _fields_ = [("gain", C.c_int64), ("ideal_gain", C.c_int64), ("slo_attained", C.c_int32), ("finished", C.c_int32),
                 ("steps", C.c_int32), ("reserved", C.c_int32), ("end_ps", C.c_int64)]
@@ -356,18 +359,19 @@ def ps_sched_simulate(cfg: dict, dev_free_order, host_free_order, trace, max_ste
     token_times (one int64 array per request, in the order of `trace`)."""
     c = _sched_cfg(cfg)
     d, h = _i32(dev_free_order), _i32(host_free_order)
-    tr = (ps_trace_req * max(len(trace), 1))()
-    for i, p in enumerate(trace):
-        tr[i] = ps_trace_req(p.rid, p.arrival_ps, p.prio, p.prompt_len, p.out_len, 0)
+    rec = np.zeros(max(len(trace), 1), dtype=_TRACE_DTYPE)   # column by column: a tenth of the time of one struct per request
+    for name in ("rid", "arrival_ps", "prio", "prompt_len", "out_len"):
+        rec[name][:len(trace)] = [getattr(p, name) for p in trace]
+    tr = rec.ctypes.data_as(C.POINTER(ps_trace_req))
     offs = np.zeros(len(trace) + 1, dtype=np.int64)
-    offs[1:] = np.cumsum([p.out_len for p in trace])
+    np.cumsum(rec["out_len"][:len(trace)], out=offs[1:])
     times = np.zeros(max(int(offs[-1]), 1), dtype=np.int64)
     counts = np.zeros(max(len(trace), 1), dtype=np.int32)
     out = ps_sim_result()
     _check(lib().ps_sched_simulate(C.byref(c), _i32p(d), len(d), _i32p(h), len(h), tr, len(trace), max_steps,
                                    times.ctypes.data_as(C.POINTER(C.c_int64)), _i32p(counts), C.byref(out)))
     res = {n: getattr(out, n) for n, _ in ps_sim_result._fields_ if n != "reserved"}
-    res["token_times"] = [times[offs[i]:offs[i] + counts[i]].copy() for i in range(len(trace))]
+    res["token_times"] = [times[a:a + n] for a, n in zip(offs.tolist(), counts.tolist()[:len(trace)])]
     return res
 
 

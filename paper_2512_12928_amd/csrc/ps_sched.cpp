@@ -1,12 +1,14 @@
 // Host-only batch former behind ps_sched_* / ps_form_batch: SlideBatching (Alg. 1) with the
 // eviction, offload and copy-budget rules of Sec. 4.3.  Integer picoseconds, exact arithmetic.
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <new>
 #include <string>
 #include <unordered_map>
+#include <unordered_set>
 #include <vector>
 
 #include "../../include/ps.h"
@@ -23,6 +25,7 @@ int sched_fail(int code, const char* fmt, ...);
 struct Req {
   int64_t rid, arrival;
   int32_t prio, prompt_len, out_len;
+  int32_t tag = -1;       // the caller's index of the request (ps_sched_simulate), not used by the rounds
   int64_t computed = 0;   // tokens whose KV exists (on the device, or on the host if evicted)
   int64_t generated = 0;  // output tokens delivered
   int64_t last_sched = 0;
@@ -31,7 +34,7 @@ struct Req {
   std::vector<int64_t> host_round;  // the scheduling round that issued each of them
   // per-round scratch
   int64_t exec = 0, remain = 0, weight = 0;
-  bool urgent = false, starving = false, in_batch = false, evicted_now = false;
+  bool decoding = false, urgent = false, starving = false, in_batch = false, evicted_now = false, done = false;
 
   int64_t need() const { return (int64_t)prompt_len + generated; }
   int64_t b_miss() const {  // max(0, b_host - b_device)
@@ -42,11 +45,23 @@ struct Req {
 
 }  // namespace
 
+// One entry of the queue while it is being ordered: the sort key of its request next to it, so that a comparison reads
+// nothing but the two entries (except where two densities are too close for doubles).
+struct OrderKey {
+  int32_t group;  // 0 starving, 1 URGENT, 2 NORMAL, 3 arrival order only
+  double density; // group 1: weight / exec, rounded
+  int64_t k;      // group 0: time last scheduled; group 2: remaining time
+  Req* r;
+};
+
 struct ps_sched {
   ps_sched_cfg cfg;
   std::vector<int32_t> dev_free, host_free;  // LIFO: back() is handed out next
   std::unordered_map<int64_t, Req*> by_id;
-  std::vector<Req*> reqs;  // active requests
+  std::vector<Req*> reqs;  // active requests, in the order of the last round, new ones behind
+  std::vector<OrderKey> keys;                        // scratch of a round
+  std::vector<Req*> Q;
+  std::vector<std::pair<Req*, int64_t>> members;
   int64_t round = 0;        // ps_form_batch calls so far
   int64_t done_upto = 0;    // offloads issued in rounds <= this have completed (ps_sched_offloads_done)
   // result storage
@@ -64,8 +79,9 @@ inline int64_t t_decode(const ps_sched_cfg& c, int64_t lkv) { return c.a_d * lkv
 
 // GetMaxChunk: largest c in [0, lq] with T~_p(c, lkv) <= T (the cost is non-decreasing in c).
 int64_t max_chunk(const ps_sched_cfg& c, int64_t lq, int64_t lkv, int64_t T) {
-  if (lq <= 0 || T < 0) return 0;
-  int64_t lo = 0, hi = lq;  // cost(lo) <= T always holds for lo = 0
+  if (lq <= 0 || T < 0 || t_prefill(c, 1, lkv) > T) return 0;
+  if (t_prefill(c, lq, lkv) <= T) return lq;
+  int64_t lo = 1, hi = lq - 1;  // cost(lo) <= T holds for lo = 1
   while (lo < hi) {
     const int64_t mid = lo + (hi - lo + 1) / 2;
     if (t_prefill(c, mid, lkv) <= T)
@@ -97,6 +113,64 @@ int64_t copy_budget(const ps_sched_cfg& c, int64_t t_budget, int64_t t_fwd_min, 
 }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Alg. 1 line 13 and the starvation rule: starving (longest wait first), URGENT by density descending, NORMAL by
+// remaining time ascending; ties by arrival, then id.  A total order, so every sorting algorithm gives the same queue.
+bool before(const OrderKey& a, const OrderKey& b) {
+  if (a.group != b.group) return a.group < b.group;
+  if (a.group == 1) {
+    const double diff = a.density - b.density;
+    if (std::fabs(diff) > 1e-14 * (std::fabs(a.density) + std::fabs(b.density))) return diff > 0;
+    const i128 da = (i128)a.r->weight * std::max<int64_t>(b.r->exec, 1);  // a.w/a.exec vs b.w/b.exec
+    const i128 db = (i128)b.r->weight * std::max<int64_t>(a.r->exec, 1);
+    if (da != db) return da > db;
+  } else if (a.k != b.k) {
+    return a.k < b.k;
+  }
+  if (a.r->arrival != b.r->arrival) return a.r->arrival < b.r->arrival;
+  return a.r->rid < b.r->rid;
+}
+
+// Sorts the queue, which comes in the order of the round before with new requests behind: from one round to the next few
+// requests change places, so an insertion sort is little more than a pass over the keys.  A request that moves usually
+// moves far (its group changes): its place is found by bisection and the keys in between move as one run.  When more than
+// a third of the requests have moved, a full sort takes over.
+void order_queue(std::vector<OrderKey>& keys) {
+  size_t moves_left = keys.size() / 3 + 16;
+  for (size_t i = 1; i < keys.size(); ++i) {
+    if (!before(keys[i], keys[i - 1])) continue;
+    if (moves_left-- == 0) {
+      std::sort(keys.begin(), keys.end(), before);
+      return;
+    }
+    const OrderKey x = keys[i];
+    const auto at = std::upper_bound(keys.begin(), keys.begin() + (ptrdiff_t)i, x, before);
+    std::move_backward(at, keys.begin() + (ptrdiff_t)i, keys.begin() + (ptrdiff_t)i + 1);
+    *at = x;
+  }
+}
+
+// Whether a list of block ids names one twice: a table of marks where the ids span a range not much longer than the
+// list (a pool is usually a permutation of 0..n-1), a sort otherwise.
+bool has_duplicate(const int32_t* ids, int32_t n) {
+  if (n < 2) return false;
+  int32_t lo = ids[0], hi = ids[0];
+  for (int32_t i = 1; i < n; ++i) {
+    lo = std::min(lo, ids[i]);
+    hi = std::max(hi, ids[i]);
+  }
+  const int64_t span = (int64_t)hi - lo + 1;
+  if (span < n) return true;
+  if (span <= 16 * (int64_t)n + 1024) {
+    std::vector<uint8_t> seen((size_t)span, 0);
+    for (int32_t i = 0; i < n; ++i)
+      if (seen[(size_t)((int64_t)ids[i] - lo)]++) return true;
+    return false;
+  }
+  std::vector<int32_t> v(ids, ids + n);
+  std::sort(v.begin(), v.end());
+  return std::adjacent_find(v.begin(), v.end()) != v.end();
+}
 
 }  // namespace
 
@@ -133,19 +207,15 @@ int ps_sched_create(const ps_sched_cfg* cfg, const int32_t* dev_free_order, int3
     return sched_fail(PS_EINVAL, "bad pool description");
   for (int p = 0; p < cfg->n_classes; ++p)
     if (cfg->class_weight[p] <= 0) return sched_fail(PS_EINVAL, "class weights must be positive");
-  for (int pass = 0; pass < 2; ++pass) {
-    std::vector<int32_t> v(pass == 0 ? dev_free_order : host_free_order,
-                           (pass == 0 ? dev_free_order : host_free_order) + (pass == 0 ? n_dev : n_host));
-    std::sort(v.begin(), v.end());
-    if (std::adjacent_find(v.begin(), v.end()) != v.end()) return sched_fail(PS_EINVAL, "duplicate block id in a pool");
-  }
+  if (has_duplicate(dev_free_order, n_dev) || has_duplicate(host_free_order, n_host))
+    return sched_fail(PS_EINVAL, "duplicate block id in a pool");
   ps_sched* s = new (std::nothrow) ps_sched();
   if (!s) return sched_fail(PS_ENOMEM, "out of host memory");
   s->cfg = *cfg;
-  s->dev_free.assign(dev_free_order, dev_free_order + n_dev);
-  std::reverse(s->dev_free.begin(), s->dev_free.end());
-  s->host_free.assign(host_free_order, host_free_order + n_host);
-  std::reverse(s->host_free.begin(), s->host_free.end());
+  s->dev_free.resize((size_t)n_dev);
+  std::reverse_copy(dev_free_order, dev_free_order + n_dev, s->dev_free.begin());
+  s->host_free.resize((size_t)n_host);
+  std::reverse_copy(host_free_order, host_free_order + n_host, s->host_free.begin());
   *out = s;
   return PS_OK;
 }
@@ -190,8 +260,10 @@ int ps_sched_offloads_done(ps_sched* s, int64_t upto_round) {
   return PS_OK;
 }
 
-int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
-  if (!s || !out) return sched_fail(PS_EINVAL, "ps_form_batch: NULL argument");
+// One round.  want_batch false: the batch's token offsets and block tables, the queue's order and the lists of blocks
+// to copy, which only a caller that runs the batch needs, are not written out (the simulation delivers tokens and takes
+// the number of offloaded blocks, nothing else).
+static int form_round(ps_sched* s, int64_t now, bool want_batch, ps_batch_out* out) {
   s->round += 1;
   const ps_sched_cfg& c = s->cfg;
   const int64_t blk = c.block_tokens;
@@ -203,18 +275,21 @@ int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
   std::memset(out, 0, sizeof *out);
 
   // queue = requests that have arrived
-  std::vector<Req*> Q;
+  std::vector<Req*>& Q = s->Q;
+  Q.clear();
   for (Req* r : s->reqs)
     if (r->arrival <= now) Q.push_back(r);
 
   int64_t t_budget = 0, phi = 0, b_copy = 0, t_batch = 0;
-  std::vector<std::pair<Req*, int64_t>> members;
+  std::vector<std::pair<Req*, int64_t>>& members = s->members;
+  members.clear();
   if (!Q.empty()) {
     // Alg. 1 lines 1-6: exec, remain, density (as weight / exec), t_min
     int64_t t_min = INT64_MAX, sum_exec = 0, b_missing = 0;
     for (Req* r : Q) {
       const int64_t lq = r->need() - r->computed;
       const bool dec = r->generated >= 1 && lq == 1;
+      r->decoding = dec && r->host_slots.size() <= r->dev_blocks.size();  // and nothing of it is on the host only
       r->exec = dec ? t_decode(c, r->need()) : t_prefill(c, lq, r->computed);
       const int64_t i = r->generated + 1;  // index of the next token to deliver
       r->remain = c.ttft_slo_ps + (i - 1) * c.tpot_slo_ps - (now - r->arrival);
@@ -232,39 +307,53 @@ int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
       r->urgent = (i128)r->remain * c.gamma_den < (i128)c.gamma_num * phi;
       r->starving = now - r->last_sched > c.tau_ps;
     }
-    // line 13 and the starvation rule: starving (longest wait first), URGENT by density
-    // descending, NORMAL by remaining time ascending; ties by arrival, then id
+    // line 13 and the starvation rule (see before())
     const bool fcfs = c.order_policy == PS_ORDER_FCFS;  // comparison arm: arrival order, nothing else
-    auto group = [&](const Req* r) { return fcfs ? 3 : (r->starving ? 0 : (r->urgent ? 1 : 2)); };
-    std::sort(Q.begin(), Q.end(), [&](const Req* a, const Req* b) {
-      const int ga = group(a), gb = group(b);
-      if (ga != gb) return ga < gb;
-      if (ga == 0) {
-        const int64_t wa = now - a->last_sched, wb = now - b->last_sched;
-        if (wa != wb) return wa > wb;
-      } else if (ga == 1) {
-        const i128 da = (i128)a->weight * std::max<int64_t>(b->exec, 1);  // a.w/a.exec vs b.w/b.exec
-        const i128 db = (i128)b->weight * std::max<int64_t>(a->exec, 1);
-        if (da != db) return da > db;
-      } else if (ga == 2) {
-        if (a->remain != b->remain) return a->remain < b->remain;
-      }
-      if (a->arrival != b->arrival) return a->arrival < b->arrival;
-      return a->rid < b->rid;
-    });
+    std::vector<OrderKey>& keys = s->keys;
+    keys.clear();
     for (Req* r : Q) {
-      s->order.push_back(r->rid);
-      if (r->urgent) s->urgent.push_back(r->rid);
+      OrderKey k;
+      k.group = fcfs ? 3 : (r->starving ? 0 : (r->urgent ? 1 : 2));
+      k.density = k.group == 1 ? (double)r->weight / (double)std::max<int64_t>(r->exec, 1) : 0.0;
+      k.k = k.group == 0 ? r->last_sched : (k.group == 2 ? r->remain : 0);
+      k.r = r;
+      keys.push_back(k);
     }
+    order_queue(keys);
+    for (size_t i = 0; i < Q.size(); ++i) Q[i] = keys[i].r;
+    {  // the active requests take over this order; those that have not arrived yet follow
+      size_t w = Q.size();
+      if (w != s->reqs.size()) {
+        std::vector<Req*> later;
+        for (Req* r : s->reqs)
+          if (r->arrival > now) later.push_back(r);
+        std::copy(later.begin(), later.end(), s->reqs.begin() + (ptrdiff_t)w);
+      }
+      std::copy(Q.begin(), Q.end(), s->reqs.begin());
+    }
+    if (want_batch)
+      for (Req* r : Q) {
+        s->order.push_back(r->rid);
+        if (r->urgent) s->urgent.push_back(r->rid);
+      }
     // line 14
     b_copy = copy_budget(c, t_budget, c.t_c + sum_exec, b_missing);
     int64_t b_rem = b_copy;
     // lines 15-23
     t_batch = c.t_c;
     size_t idx = 0;
+    size_t tail = Q.size();  // requests from here on have been looked at as victims: none becomes one later in the round
     while (idx < Q.size() && t_batch < t_budget) {
       Req* r = Q[idx++];
       if (r->evicted_now) continue;
+      if (r->decoding && r->need() <= (int64_t)r->dev_blocks.size() * blk) {  // a decode token that needs no block: most of a round
+        r->computed += 1;
+        r->last_sched = now;
+        r->in_batch = true;
+        t_batch += r->exec;
+        members.emplace_back(r, 1);
+        continue;
+      }
       const int64_t T = t_budget - t_batch;
       const int64_t miss = r->b_miss();
       int64_t k = 0, comp = r->computed;
@@ -278,7 +367,7 @@ int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
       int64_t chunk, t;
       if (dec) {
         chunk = 1;  // a decode token is atomic
-        t = t_decode(c, r->need());
+        t = miss > 0 ? t_decode(c, r->need()) : r->exec;
       } else {
         chunk = max_chunk(c, lq, comp, T);
         if (chunk == 0) continue;
@@ -292,17 +381,16 @@ int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
       int64_t want = ceil_div(comp + chunk, blk) - held;
       if (want > (int64_t)s->dev_free.size()) {
         // victims from the tail of the sorted queue, behind r, never a near-starved request
-        for (size_t j = Q.size(); j-- > idx && want > (int64_t)s->dev_free.size();) {
-          Req* v = Q[j];
+        while (tail > idx && want > (int64_t)s->dev_free.size()) {
+          Req* v = Q[--tail];
           if (v->in_batch || v->evicted_now || v->dev_blocks.empty()) continue;
           if ((i128)(now - v->last_sched) * c.rho_den >= (i128)c.rho_num * c.tau_ps) continue;
-          for (int32_t b : v->dev_blocks) s->dev_free.push_back(b);
+          s->dev_free.insert(s->dev_free.end(), v->dev_blocks.begin(), v->dev_blocks.end());
           v->dev_blocks.clear();
           // host copies still in flight are discarded with the eviction (Sec. 4.3, Asynchronous
           // Offloading): only completed ones keep their tokens from being recomputed
-          size_t conf = 0;
-          while (conf < v->host_round.size() && v->host_round[conf] <= s->done_upto) ++conf;
-          for (size_t b = conf; b < v->host_slots.size(); ++b) s->host_free.push_back(v->host_slots[b]);
+          const size_t conf = (size_t)(std::upper_bound(v->host_round.begin(), v->host_round.end(), s->done_upto) - v->host_round.begin());
+          s->host_free.insert(s->host_free.end(), v->host_slots.begin() + (ptrdiff_t)conf, v->host_slots.end());
           v->host_slots.resize(conf);
           v->host_round.resize(conf);
           v->computed = std::min<int64_t>(v->computed, (int64_t)conf * blk);
@@ -319,26 +407,22 @@ int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
       }
       // admit
       if (miss > 0) {
-        std::vector<int32_t> fresh;
-        for (int64_t b = 0; b < k; ++b) {
-          fresh.push_back(s->dev_free.back());
-          s->dev_free.pop_back();
+        r->dev_blocks.assign(s->dev_free.rbegin(), s->dev_free.rbegin() + (ptrdiff_t)k);
+        s->dev_free.resize(s->dev_free.size() - (size_t)k);
+        if (want_batch) {
+          s->si_host.insert(s->si_host.end(), r->host_slots.begin(), r->host_slots.begin() + (ptrdiff_t)k);
+          s->si_dev.insert(s->si_dev.end(), r->dev_blocks.begin(), r->dev_blocks.end());
         }
-        for (int64_t b = 0; b < k; ++b) {
-          s->si_host.push_back(r->host_slots[(size_t)b]);
-          s->si_dev.push_back(fresh[(size_t)b]);
-        }
-        for (size_t b = (size_t)k; b < r->host_slots.size(); ++b) s->host_free.push_back(r->host_slots[b]);
+        s->host_free.insert(s->host_free.end(), r->host_slots.begin() + (ptrdiff_t)k, r->host_slots.end());
         r->host_slots.resize((size_t)k);
         r->host_round.resize((size_t)k);
-        r->dev_blocks = fresh;
         r->computed = comp;
         b_rem -= k;
         want -= k;
       }
-      for (int64_t b = 0; b < want; ++b) {
-        r->dev_blocks.push_back(s->dev_free.back());
-        s->dev_free.pop_back();
+      if (want > 0) {
+        r->dev_blocks.insert(r->dev_blocks.end(), s->dev_free.rbegin(), s->dev_free.rbegin() + (ptrdiff_t)want);
+        s->dev_free.resize(s->dev_free.size() - (size_t)want);
       }
       r->computed += chunk;
       r->last_sched = now;
@@ -352,56 +436,65 @@ int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
   // the batch as the attention layer takes it, in admission order
   s->q_start.push_back(0);
   s->bt_start.push_back(0);
-  for (auto& mc : members) {
-    Req* r = mc.first;
-    s->req_ids.push_back(r->rid);
-    s->q_start.push_back(s->q_start.back() + (int32_t)mc.second);
-    s->kv_len.push_back((int32_t)r->computed);
-    const int64_t nb = ceil_div(r->computed, blk);
-    for (int64_t b = 0; b < nb; ++b) s->block_ids.push_back(r->dev_blocks[(size_t)b]);
-    s->bt_start.push_back((int32_t)s->block_ids.size());
-    s->prio.push_back((uint8_t)r->prio);
-  }
+  if (want_batch)
+    for (auto& mc : members) {
+      Req* r = mc.first;
+      s->req_ids.push_back(r->rid);
+      s->q_start.push_back(s->q_start.back() + (int32_t)mc.second);
+      s->kv_len.push_back((int32_t)r->computed);
+      const int64_t nb = ceil_div(r->computed, blk);
+      s->block_ids.insert(s->block_ids.end(), r->dev_blocks.begin(), r->dev_blocks.begin() + (ptrdiff_t)nb);
+      s->bt_start.push_back((int32_t)s->block_ids.size());
+      s->prio.push_back((uint8_t)r->prio);
+    }
   // token delivery at now + T_pd(B), completion
   for (auto& mc : members) {
     Req* r = mc.first;
     if (r->computed != r->need()) continue;
     r->generated += 1;
-    s->emitted_req.push_back(r->rid);
+    s->emitted_req.push_back(want_batch ? r->rid : r->tag);
     s->emitted_index.push_back((int32_t)r->generated);
     if (r->generated == r->out_len) {
-      for (int32_t b : r->dev_blocks) s->dev_free.push_back(b);
-      for (int32_t h : r->host_slots) s->host_free.push_back(h);
+      r->done = true;
+      s->dev_free.insert(s->dev_free.end(), r->dev_blocks.begin(), r->dev_blocks.end());
+      s->host_free.insert(s->host_free.end(), r->host_slots.begin(), r->host_slots.end());
       r->dev_blocks.clear();
       r->host_slots.clear();
       r->host_round.clear();
-      s->finished.push_back(r->rid);
+      s->finished.push_back(want_batch ? r->rid : r->tag);
     }
   }
   // asynchronous offload: every n_off^r newly completed full blocks of r get a host copy
+  int32_t n_offloaded = 0;
   for (auto& mc : members) {
     Req* r = mc.first;
-    if (r->generated == r->out_len && r->dev_blocks.empty()) continue;  // finished above
-    const int64_t full = r->computed / blk;
-    const int64_t pending = full - (int64_t)r->host_slots.size();
+    if (r->done) continue;
     int64_t n_off = (int64_t)c.n_off_base >> (r->prio - 1);
     if (n_off < 1) n_off = 1;
-    if (pending >= n_off && (int64_t)s->host_free.size() >= pending) {
-      for (int64_t b = (int64_t)r->host_slots.size(); b < full; ++b) {
-        const int32_t h = s->host_free.back();
-        s->host_free.pop_back();
-        r->host_slots.push_back(h);
-        r->host_round.push_back(s->round);
-        s->so_dev.push_back(r->dev_blocks[(size_t)b]);
-        s->so_host.push_back(h);
-      }
+    const int64_t copied = (int64_t)r->host_slots.size();
+    if (r->computed < (copied + n_off) * blk) continue;  // fewer than n_off full blocks without a host copy
+    const int64_t pending = r->computed / blk - copied;
+    if ((int64_t)s->host_free.size() < pending) continue;
+    r->host_slots.insert(r->host_slots.end(), s->host_free.rbegin(), s->host_free.rbegin() + (ptrdiff_t)pending);
+    s->host_free.resize(s->host_free.size() - (size_t)pending);
+    r->host_round.insert(r->host_round.end(), (size_t)pending, s->round);
+    n_offloaded += (int32_t)pending;
+    if (want_batch) {
+      s->so_dev.insert(s->so_dev.end(), r->dev_blocks.begin() + (ptrdiff_t)copied, r->dev_blocks.begin() + (ptrdiff_t)(copied + pending));
+      s->so_host.insert(s->so_host.end(), r->host_slots.end() - (ptrdiff_t)pending, r->host_slots.end());
     }
   }
-  for (int64_t rid : s->finished) {
-    Req* r = s->by_id[rid];
-    s->by_id.erase(rid);
-    s->reqs.erase(std::find(s->reqs.begin(), s->reqs.end(), r));
-    delete r;
+  if (!s->finished.empty()) {
+    size_t w = 0;
+    for (Req* r : s->reqs) {
+      if (!r->done) {
+        s->reqs[w++] = r;
+        continue;
+      }
+      s->by_id.erase(r->rid);
+      delete r;
+    }
+    s->reqs.resize(w);
   }
 
   out->batch.n_req = (int32_t)members.size();
@@ -423,7 +516,7 @@ int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
   out->n_swap_in = (int32_t)s->si_host.size();
   out->swap_in_host_slots = s->si_host.data();
   out->swap_in_dev_blocks = s->si_dev.data();
-  out->n_swap_out = (int32_t)s->so_dev.size();
+  out->n_swap_out = n_offloaded;
   out->swap_out_dev_blocks = s->so_dev.data();
   out->swap_out_host_slots = s->so_host.data();
   out->n_evicted = (int32_t)s->evicted.size();
@@ -435,6 +528,11 @@ int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
   out->finished = s->finished.data();
   out->round = s->round;
   return PS_OK;
+}
+
+int ps_form_batch(ps_sched* s, int64_t now, ps_batch_out* out) {
+  if (!s || !out) return sched_fail(PS_EINVAL, "ps_form_batch: NULL argument");
+  return form_round(s, now, true, out);
 }
 
 // Eq. 3 and the two metrics of Sec. 5.1 for one request.
@@ -473,11 +571,12 @@ int ps_sched_simulate(const ps_sched_cfg* cfg, const int32_t* dev_free_order, in
   // arrival order (ties by id); where each request's token times go
   std::vector<int32_t> by_arrival((size_t)n_trace);
   std::vector<int64_t> t_off((size_t)n_trace + 1, 0);
-  std::unordered_map<int64_t, int32_t> index_of;
+  std::unordered_set<int64_t> ids;
+  ids.reserve((size_t)n_trace);
   for (int32_t i = 0; i < n_trace; ++i) {
     by_arrival[(size_t)i] = i;
     t_off[(size_t)i + 1] = t_off[(size_t)i] + std::max(trace[i].out_len, 0);
-    if (!index_of.emplace(trace[i].rid, i).second) {
+    if (!ids.insert(trace[i].rid).second) {
       ps_sched_destroy(s);
       return sched_fail(PS_EINVAL, "ps_sched_simulate: duplicate request id %lld", (long long)trace[i].rid);
     }
@@ -512,6 +611,7 @@ int ps_sched_simulate(const ps_sched_cfg* cfg, const int32_t* dev_free_order, in
         ps_sched_destroy(s);
         return rc;
       }
+      s->reqs.back()->tag = by_arrival[(size_t)nxt];  // what form_round reports in place of the id
       ++nxt;
     }
     if (s->reqs.empty()) {
@@ -521,23 +621,19 @@ int ps_sched_simulate(const ps_sched_cfg* cfg, const int32_t* dev_free_order, in
     }
     while (inflight_head < inflight.size() && inflight[inflight_head].second <= now)
       (void)ps_sched_offloads_done(s, inflight[inflight_head++].first);
-    rc = ps_form_batch(s, now, &fb);
-    if (rc != PS_OK) {
-      ps_sched_destroy(s);
-      return rc;
-    }
+    (void)form_round(s, now, false, &fb);
     ++steps;
     if (fb.n_swap_out > 0) {
       copy_free_at = std::max(copy_free_at, now + fb.t_batch_ps) + (int64_t)fb.n_swap_out * cfg->t_block_ps;
       inflight.emplace_back(fb.round, copy_free_at);
     }
     for (int32_t e = 0; e < fb.n_emitted; ++e) {  // tokens are delivered when the batch ends
-      const int32_t i = index_of[fb.emitted_req[e]];
+      const int32_t i = (int32_t)fb.emitted_req[e];
       token_times[t_off[(size_t)i] + n_delivered[i]] = now + fb.t_batch_ps - trace[i].arrival_ps;
       n_delivered[i] += 1;
     }
     for (int32_t f = 0; f < fb.n_finished; ++f) {
-      const int32_t i = index_of[fb.finished[f]];
+      const int32_t i = (int32_t)fb.finished[f];
       int64_t g = 0, ideal = 0;
       int32_t ok = 0;
       (void)ps_tdg_score(cfg, trace[i].prio, trace[i].out_len, token_times + t_off[(size_t)i], n_delivered[i], &g, &ideal, &ok);

@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from typing import Optional, Tuple
 
 import numpy as np
@@ -117,7 +118,7 @@ def lib():
         L.ps_step_next_layer.argtypes = [C.c_void_p] + [C.c_void_p] * 6 + [C.c_size_t, C.c_void_p, C.c_uint64]
         L.ps_set_profiling.argtypes = [C.c_void_p, C.c_int]
         L.ps_get_step_times.argtypes = [C.c_void_p, C.POINTER(ps_step_times)]
-        swap_args = [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.c_int32, C.c_int32, C.c_void_p,
+        swap_args = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p,
                      C.c_void_p, C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_uint64)]
         L.ps_swap_out.argtypes = swap_args
         L.ps_swap_in.argtypes = swap_args
@@ -151,19 +152,11 @@ def _check(rc: int, ok=(PS_OK,)) -> int:
 
 
 def _ptr(x) -> Optional[int]:
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return x
-    return int(x.data_ptr())
+    return x if x is None or isinstance(x, int) else x.data_ptr()
 
 
 def _stream(s) -> Optional[int]:
-    if s is None:
-        return None
-    if isinstance(s, int):
-        return s
-    return int(s.cuda_stream)
+    return s if s is None or isinstance(s, int) else s.cuda_stream
 
 
 def _i32(a) -> np.ndarray:
@@ -172,6 +165,18 @@ def _i32(a) -> np.ndarray:
 
 def _i32p(a: np.ndarray):
     return a.ctypes.data_as(C.POINTER(C.c_int32))
+
+
+def _addr(a: np.ndarray) -> int:
+    """Address of an array's first element; a third of the time of ``a.ctypes.data`` where the array can be written to."""
+    try:
+        return C.addressof(C.c_char.from_buffer(a))
+    except (TypeError, ValueError, BufferError):      # read-only, or empty
+        return a.ctypes.data
+
+
+_pack_batch = struct.Struct("@iiPPPPP").pack
+assert struct.calcsize("@iiPPPPP") == C.sizeof(ps_batch)
 
 
 def ps_create(n_q_heads: int, n_kv_heads: int, n_device_blocks: int, n_host_blocks: int = 0,
@@ -206,9 +211,12 @@ def make_batch(q_start, kv_len, bt_start, block_ids, prio=None):
     """Builds the C struct; returns (struct, keepalive) -- keep both until the call returns."""
     qs, kv, bs, ids = _i32(q_start), _i32(kv_len), _i32(bt_start), _i32(block_ids)
     pr = None if prio is None else np.ascontiguousarray(prio, dtype=np.uint8)
-    b = ps_batch(len(kv), int(qs[-1]) if len(qs) else 0, _i32p(qs), _i32p(kv), _i32p(bs), _i32p(ids),
-                 None if pr is None else pr.ctypes.data_as(C.POINTER(C.c_uint8)))
-    return b, (qs, kv, bs, ids, pr)
+    # the struct's bytes in one go: building it from typed pointers took 7 us, as long as a small step's kernels
+    b = ps_batch.from_buffer_copy(_pack_batch(len(kv), qs.item(-1) if len(qs) else 0, _addr(qs), _addr(kv), _addr(bs), _addr(ids),
+                                              0 if pr is None else _addr(pr)))
+    keep = (qs, kv, bs, ids, pr)
+    b._arrays = keep
+    return b, keep
 
 
 def ps_step(ctx: int, batch, q, k_new, v_new, kv_cache, out, workspace, workspace_bytes: int,
@@ -308,7 +316,7 @@ def _swap(fn, ctx, first_ids, second_ids, copy_budget, a, b, stream) -> Tuple[in
     if len(x) != len(y):
         raise ValueError("id lists differ in length")
     n_done, ticket = C.c_int32(), C.c_uint64()
-    _check(fn(ctx, _i32p(x), _i32p(y), len(x), copy_budget, _ptr(a), _ptr(b), _stream(stream),
+    _check(fn(ctx, _addr(x), _addr(y), len(x), copy_budget, _ptr(a), _ptr(b), _stream(stream),
               C.byref(n_done), C.byref(ticket)))
     return n_done.value, ticket.value
 

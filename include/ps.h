@@ -222,7 +222,8 @@ int ps_step_static(ps_ctx* ctx, const ps_batch* batch, const void* q, const void
 
 /* Host only, no device needed: the decode work list ps_step builds for the decode requests (l_q == 1)
  * of `batch` when `waves` decode waves are available (ps_step itself uses four per compute unit for
- * a decode-only batch and a share of that next to prefill work). The list: the requests'
+ * a decode-only batch and a share of that next to prefill work; for a decode-only batch of few or short requests it
+ * may give every request workgroups of its own instead, see ps_plan_launch). The list: the requests'
  * 32-token KV tiles, laid end to end in batch order, are cut into n_slots = min(waves / n_kv_heads,
  * tiles / 16) slots of equal length (to within one tile); each (slot, kv-head) is walked by one wave.
  * With cfg.decode_chunk > 0: fixed partitions of that many tokens, one per slot, longest first.
@@ -238,8 +239,10 @@ int ps_plan_decode(const ps_layer_cfg* cfg, const ps_batch* batch, int32_t waves
  * compute units (the decode work and the prefill work of a mixed batch share one launch; the decode
  * workgroups, one compute unit each, come first and the prefill workgroups take the rest and inherit the
  * decode units as those finish). For tests of that host logic.
- *   out6[0] decode waves     out6[1] decode slots (waves / Hkv)
- *   out6[2] decode workgroups; 0 for a mixed batch whose workgroups carry both kinds of work (cfg.mixed_launch):
+ * A decode-only batch whose time is latency rather than bytes (few or short requests) is laid out by request: every
+ * segment (a request, or one of the equal parts a long one is cut into) gets a workgroup of 4 or 8 waves per kv-head.
+ *   out6[0] decode waves     out6[1] decode slots (waves / Hkv); laid out by request: segments, and workgroups
+ *   out6[2] decode workgroups (four slots each; laid out by request, one segment each); 0 for a mixed batch whose workgroups carry both kinds of work (cfg.mixed_launch):
  *           then every prefill workgroup also walks up to two of the decode slots
  *   out6[3] prefill workgroups     out6[4] KV tiles (64 tokens) per partition of split prefill rows, 0 = no row split
  *   out6[5] split-K partial slots the step uses

@@ -81,6 +81,11 @@ struct DecodePlan {
   std::vector<ps::DecodeItem> ditems;
   std::vector<int32_t> dslots;  // slot x owns ditems[dslots[x] .. dslots[x+1])
   std::vector<ps::MergeItem> mitems;
+  std::vector<int> scratch;
+  std::vector<double> bins;
+  std::vector<ps::RequestItem> ritems;  // what goes to the device in the place of ditems if request_waves > 0
+  int longest_merge = 0;                // partitions of the merge item that has most
+  int request_waves = 0;  // > 0: every item is walked by workgroups of its own, of this many waves (decode_request_kernel)
 };
 
 struct ps_ctx {
@@ -361,7 +366,7 @@ void build_decode_slots(DecodePlan* c, int n_kv_heads, int decode_chunk, const p
   };
   auto item = [&](int r, int t0, int t1, int part) {
     const int L = b->kv_len[r];
-    return ps::DecodeItem{b->bt_start[r], b->q_start[r], t0, t1, part, (L + ps::kBlockTokens - 1) / ps::kBlockTokens, {0, 0}};
+    return ps::DecodeItem{b->bt_start[r], b->q_start[r], t0, t1, part, (L + ps::kBlockTokens - 1) / ps::kBlockTokens, t1 == L, 0};
   };
   if (decode_chunk > 0) {
     const int CH = decode_chunk;
@@ -412,6 +417,128 @@ void build_decode_slots(DecodePlan* c, int n_kv_heads, int decode_chunk, const p
   close_slot();
 }
 
+// Decode-only batches of few requests: should every segment get workgroups of its own (decode_request_kernel), and which
+// segments?  Priced, in us, from what the kernels take on an MI355X:
+//  - a launch whose workgroups walk next to nothing takes 4.2 (launch, item, first tile, one meeting in LDS), the slot
+//    launch with its merge 9.5; a slot takes 0.9 per tile and 2 for every request in it;
+//  - a further workgroup on the same place costs 5;
+//  - a compute unit takes in a tile's 16 KiB every 0.36 us (45 GB/s) however many waves ask; the whole chip takes
+//    plan_stream_TBps (8 % less in this launch): while more units are busy than that rate feeds, a tile takes longer;
+//  - a merge launch, needed once any request is cut, takes 3.
+// Candidates: workgroups of 8 waves (one per compute unit) or 4 (two per unit), requests whole or cut into equal segments
+// of at most `cap` tiles, from the shortest cap at which all segments run at once.
+bool build_decode_requests(DecodePlan* c, const ps_batch* b, const std::vector<int>& reqs, int& n_parts, int n_kv_heads, int n_cus,
+                           double stream_TBps) {
+  constexpr double kLaunchUs = 4.2, kMergeUs = 3.0, kTileUs = 0.36, kAgainUs = 5.0, kStreamLoss = 1.08;
+  constexpr double kSlotLaunchUs = 9.5, kSlotTileUs = 0.9, kSlotRequestUs = 2.0;
+  const double tile_us = 4.0 * ps::kTileTokens * ps::kHeadDim / (stream_TBps * 1e6);  // of the whole chip's stream
+  std::vector<int>& len = c->scratch;                                                 // tiles of every request
+  len.clear();
+  int64_t T = 0;
+  for (int r : reqs) {
+    len.push_back((b->kv_len[r] + ps::kTileTokens - 1) / ps::kTileTokens);
+    T += len.back();
+  }
+  const double bytes_us = (double)T * n_kv_heads * tile_us;
+  if (bytes_us > 200.0) return false;  // nothing of this matters then
+  const int slots = std::max<int>(1, (int)std::min<int64_t>(ps::decode_waves_per_wg() * n_cus / n_kv_heads, T / kMinSlotTiles));
+  double best = kSlotLaunchUs + std::max(bytes_us, kSlotTileUs * (double)T / slots) + kSlotRequestUs * (double)len.size() / slots;
+  int waves = 0, cap = 0;
+  std::sort(len.begin(), len.end(), std::greater<int>());
+  const int longest = len.front();
+  std::vector<double>& bins = c->bins;
+  // the time at which a launch of the requests, cut at cp tiles, ends; `places` workgroups of a kv-head run at once
+  auto price = [&](int places, int cp) {
+    int64_t n_seg = 0;
+    bins.assign((size_t)places, 0.0);  // tiles a place has to take in
+    for (int x : len) {
+      const int np = (x + cp - 1) / cp;
+      for (int k = 0; k < np; ++k, ++n_seg) {
+        if (n_seg < places) {
+          bins[(size_t)n_seg] = (double)x / np;
+          if (n_seg + 1 == places) std::make_heap(bins.begin(), bins.end(), std::greater<double>());
+        } else {
+          std::pop_heap(bins.begin(), bins.end(), std::greater<double>());
+          bins.back() += (double)x / np;
+          std::push_heap(bins.begin(), bins.end(), std::greater<double>());
+        }
+      }
+    }
+    std::sort(bins.begin(), bins.end());
+    double us = kLaunchUs + kAgainUs * (double)((n_seg - 1) / places) + (n_seg > (int64_t)len.size() ? kMergeUs : 0.0), done = 0.0;
+    for (int i = 0; i < places; ++i) {  // places - i places are still busy while the next one runs out
+      const double busy = (double)(places - i) * n_kv_heads;
+      us += (bins[(size_t)i] - done) * std::max(kTileUs * std::max(1.0, busy / n_cus), busy * tile_us * kStreamLoss);
+      done = bins[(size_t)i];
+    }
+    return us;
+  };
+  for (int nw : {8, 4}) {
+    const int places = n_cus * 8 / nw / n_kv_heads;
+    if (places < 1 || (int64_t)len.size() > 8 * (int64_t)places) continue;
+    // the shortest cap at which all segments run at once; no shorter than a slot, which ps_workspace_bytes counts on
+    int lo = longest;
+    if ((int)len.size() <= places) {
+      lo = std::max<int>(kMinSlotTiles, (int)((T + places - 1) / places));
+      for (int hi = longest; lo < hi;) {
+        const int mid = lo + (hi - lo) / 2;
+        int64_t n = 0;
+        for (int x : len) n += (x + mid - 1) / mid;
+        if (n <= places)
+          hi = mid;
+        else
+          lo = mid + 1;
+      }
+    }
+    for (int cp = lo;; cp *= 2) {
+      cp = std::min(cp, longest);
+      const double us = price(places, cp);
+      if (us < best) {
+        best = us;
+        waves = nw;
+        cap = cp;
+      }
+      if (cp >= longest) break;
+    }
+  }
+  if (waves == 0) return false;
+  c->ditems.clear();
+  c->dslots.assign(1, 0);
+  for (int r : reqs) {
+    const int L = b->kv_len[r], n = (L + ps::kTileTokens - 1) / ps::kTileTokens;
+    const int np = (n + cap - 1) / cap;
+    if (np > 1) c->mitems.push_back(ps::MergeItem{b->q_start[r], n_parts, np, 0});
+    for (int k = 0; k < np; ++k) {
+      const int t0 = (int)((int64_t)n * k / np) * ps::kTileTokens;
+      const int t1 = (int)std::min<int64_t>(L, (int64_t)n * (k + 1) / np * ps::kTileTokens);
+      c->ditems.push_back(ps::DecodeItem{b->bt_start[r], b->q_start[r], t0, t1, np > 1 ? n_parts++ : -1,
+                                         (L + ps::kBlockTokens - 1) / ps::kBlockTokens, t1 == L, 0});
+    }
+  }
+  std::stable_sort(c->ditems.begin(), c->ditems.end(),
+                   [](const ps::DecodeItem& x, const ps::DecodeItem& y) { return x.t1 - x.t0 > y.t1 - y.t0; });
+  for (size_t i = 1; i <= c->ditems.size(); ++i) c->dslots.push_back((int32_t)i);
+  c->request_waves = waves;
+  return true;
+}
+
+// The device's form of those items: with the block ids of the first tile of every wave's share.
+void finish_request_items(DecodePlan* c, const ps_batch* b) {
+  c->ritems.resize(c->ditems.size());
+  for (size_t i = 0; i < c->ditems.size(); ++i) {
+    ps::RequestItem& o = c->ritems[i];
+    const ps::DecodeItem& it = c->ditems[i];
+    o.it = it;
+    const int n = (it.t1 - it.t0 + ps::kTileTokens - 1) / ps::kTileTokens;
+    for (int w = 0; w < 8; ++w) {
+      const int tile = w < c->request_waves ? n * w / c->request_waves : 0;
+      const int blk = std::min(it.t0 / ps::kBlockTokens + 2 * tile, it.nblk - 1);
+      o.first[w][0] = b->block_ids[it.bt_off + blk];
+      o.first[w][1] = b->block_ids[it.bt_off + std::min(blk + 1, it.nblk - 1)];
+    }
+  }
+}
+
 // Decode work list for the launch whose workgroups carry both kinds of work.  Slot x is walked by a decode wave of
 // the prefill workgroups of work item x / slots_per_item, and lasts as long as they do if its share of the decode
 // tiles is that of its work item in the prefill work: weight[x] = length of that item's tile walk.  The requests'
@@ -438,7 +565,7 @@ void build_weighted_decode_slots(DecodePlan* c, const ps_batch* b, const std::ve
   }
   auto item = [&](int r, int t0, int t1, int part) {
     const int L = b->kv_len[r];
-    return ps::DecodeItem{b->bt_start[r], b->q_start[r], t0, t1, part, (L + ps::kBlockTokens - 1) / ps::kBlockTokens, {0, 0}};
+    return ps::DecodeItem{b->bt_start[r], b->q_start[r], t0, t1, part, (L + ps::kBlockTokens - 1) / ps::kBlockTokens, t1 == L, 0};
   };
   auto close_slot = [&]() { c->dslots.push_back((int32_t)c->ditems.size()); };
   int64_t off = 0;  // tiles before the current request
@@ -511,7 +638,7 @@ struct MetaLayout {
   size_t q_start, kv_len, bt_start, block_ids, aitems, ditems, dslots, mitems, ptiles, total;
 };
 
-MetaLayout meta_layout(int n_req, size_t n_aitems, int64_t n_table, size_t n_ditems, size_t n_dslots,
+MetaLayout meta_layout(int n_req, size_t n_aitems, int64_t n_table, size_t ditem_bytes, size_t n_dslots,
                        size_t n_mitems, size_t n_ptiles) {
   MetaLayout m;
   size_t o = 0;
@@ -525,7 +652,7 @@ MetaLayout meta_layout(int n_req, size_t n_aitems, int64_t n_table, size_t n_dit
   m.bt_start = put((size_t)(n_req + 1) * 4);
   m.block_ids = put((size_t)n_table * 4);
   m.aitems = put((size_t)n_aitems * sizeof(ps::AppendItem));
-  m.ditems = put(n_ditems * sizeof(ps::DecodeItem));
+  m.ditems = put(ditem_bytes);
   m.dslots = put(n_dslots * 4);
   m.mitems = put(n_mitems * sizeof(ps::MergeItem));
   m.ptiles = put(n_ptiles * sizeof(ps::PrefillTile));
@@ -893,6 +1020,7 @@ static int plan_batch(ps_ctx* c, const ps_batch* b, bool has_new_kv, size_t work
   c->plan.ditems.clear();
   c->plan.dslots.assign(1, 0);
   c->plan.mitems.clear();
+  c->plan.request_waves = 0;
   c->ptiles.clear();
   c->aitems.clear();
   int n_parts = 0;
@@ -993,6 +1121,8 @@ static int plan_batch(ps_ctx* c, const ps_batch* b, bool has_new_kv, size_t work
       std::vector<int64_t> weight((size_t)per_item * tiles.size());
       for (size_t x = 0; x < weight.size(); ++x) weight[x] = tiles[x / (size_t)per_item].reach;
       build_weighted_decode_slots(&c->plan, b, decode_reqs, n_parts, weight);
+    } else if (c->cfg.decode_chunk == 0 && c->cfg.decode_waves == 0 && tiles.empty() && build_decode_requests(&c->plan, b, decode_reqs, n_parts, c->cfg.n_kv_heads, c->n_cus, tuning_of(c->cfg).stream_TBps)) {
+      c->aitems.clear();  // the attention launch appends
     } else {
       build_decode_slots(&c->plan, c->cfg.n_kv_heads, c->cfg.decode_chunk, b, decode_reqs, n_parts, waves);
     }
@@ -1000,6 +1130,9 @@ static int plan_batch(ps_ctx* c, const ps_batch* b, bool has_new_kv, size_t work
       return fail(PS_ESTATE, "ps_step: inconsistent decode work list (library bug)");
   }
 
+  if (c->plan.request_waves > 0) finish_request_items(&c->plan, b);
+  c->plan.longest_merge = 0;
+  for (auto& m : c->plan.mitems) c->plan.longest_merge = std::max(c->plan.longest_merge, (int)m.n_parts);
   for (auto& t : tiles) c->ptiles.push_back(t.t);
   n_parts_out = n_parts;
   if (prefill_split_out) {
@@ -1061,13 +1194,16 @@ static int launch_phases(ps_ctx* c, const char* h, size_t upload_bytes, const ps
   // HBM speed and leaves the matrix pipes idle, prefill is the opposite: they run side by side on
   // disjoint CUs).  Profiling mode 2 gives each its own launch instead.
   const int n_slots = (int)c->plan.dslots.size() - 1;
-  if (prof == 2) {
+  if (prof == 2 && c->plan.request_waves == 0) {
     PS_HIP(ps::launch_attention(P, n_slots, 0, stream, &c->prof_wgs[0], nullptr));
     PS_HIP(hipEventRecord(c->prof_ev_now()[3], stream));
     PS_HIP(ps::launch_attention(P, 0, (int)c->ptiles.size(), stream, nullptr, &c->prof_wgs[1]));
     PS_HIP(hipEventRecord(c->prof_ev_now()[4], stream));
   } else {
-    if (c->plan_fused) {
+    if (c->plan.request_waves > 0) {
+      PS_HIP(ps::launch_decode_requests(P, n_slots, c->plan.request_waves, k_new != nullptr, stream, &c->prof_wgs[0]));
+      c->prof_wgs[1] = 0;
+    } else if (c->plan_fused) {
       PS_HIP(ps::launch_fused(P, n_slots, (int)c->ptiles.size(), stream, &c->prof_wgs[1]));
       c->prof_wgs[0] = c->prof_wgs[1];
     } else {
@@ -1078,7 +1214,7 @@ static int launch_phases(ps_ctx* c, const char* h, size_t upload_bytes, const ps
       PS_HIP(hipEventRecord(c->prof_ev_now()[4], stream));
     }
   }
-  PS_HIP(ps::launch_merge(P, 0, (int)c->plan.mitems.size(), stream));
+  PS_HIP(ps::launch_merge(P, 0, (int)c->plan.mitems.size(), c->plan.longest_merge, stream));
   if (prof) {
     PS_HIP(hipEventRecord(c->prof_ev_now()[5], stream));
     ++c->prof_n;
@@ -1164,7 +1300,9 @@ static int step_impl(ps_ctx* c, const ps_batch* b, const void* q, const void* k_
     if (rc != PS_OK) return rc;
   }
 
-  const MetaLayout ml = meta_layout(n_req, c->aitems.size(), n_table, c->plan.ditems.size(), c->plan.dslots.size(),
+  const bool by_request = c->plan.request_waves > 0;  // then the items go over in their device form, and slots mean nothing
+  const size_t ditem_bytes = by_request ? c->plan.ritems.size() * sizeof(ps::RequestItem) : c->plan.ditems.size() * sizeof(ps::DecodeItem);
+  const MetaLayout ml = meta_layout(n_req, c->aitems.size(), n_table, ditem_bytes, by_request ? 0 : c->plan.dslots.size(),
                                      c->plan.mitems.size(), c->ptiles.size());
   const size_t part_bytes = align_up((size_t)n_parts * c->cfg.n_q_heads * ps::kPartStride * sizeof(float), 256);
   if (part_bytes > workspace_bytes)
@@ -1187,8 +1325,8 @@ static int step_impl(ps_ctx* c, const ps_batch* b, const void* q, const void* k_
   std::memcpy(h + ml.bt_start, b->bt_start, (size_t)(n_req + 1) * 4);
   std::memcpy(h + ml.block_ids, b->block_ids, (size_t)n_table * 4);
   if (!c->aitems.empty()) std::memcpy(h + ml.aitems, c->aitems.data(), c->aitems.size() * sizeof(ps::AppendItem));
-  if (!c->plan.ditems.empty()) std::memcpy(h + ml.ditems, c->plan.ditems.data(), c->plan.ditems.size() * sizeof(ps::DecodeItem));
-  if (!c->plan.dslots.empty()) std::memcpy(h + ml.dslots, c->plan.dslots.data(), c->plan.dslots.size() * 4);
+  if (ditem_bytes > 0) std::memcpy(h + ml.ditems, by_request ? (const void*)c->plan.ritems.data() : c->plan.ditems.data(), ditem_bytes);
+  if (!by_request && !c->plan.dslots.empty()) std::memcpy(h + ml.dslots, c->plan.dslots.data(), c->plan.dslots.size() * 4);
   if (!c->plan.mitems.empty()) std::memcpy(h + ml.mitems, c->plan.mitems.data(), c->plan.mitems.size() * sizeof(ps::MergeItem));
   if (!c->ptiles.empty()) std::memcpy(h + ml.ptiles, c->ptiles.data(), c->ptiles.size() * sizeof(ps::PrefillTile));
 
@@ -1346,9 +1484,10 @@ int ps_plan_launch(const ps_layer_cfg* cfg, const ps_batch* b, int32_t n_cus, in
   if (rc != PS_OK) return rc;
   const int n_slots = (int)c.plan.dslots.size() - 1;
   const int dw = ps::decode_waves_per_wg();
+  const bool by_request = c.plan.request_waves > 0;
   out6[0] = n_slots * cfg->n_kv_heads;
   out6[1] = n_slots;
-  out6[2] = c.plan_fused ? 0 : (n_slots > 0 ? (n_slots + dw - 1) / dw * cfg->n_kv_heads : 0);
+  out6[2] = by_request ? n_slots * cfg->n_kv_heads : c.plan_fused ? 0 : (n_slots > 0 ? (n_slots + dw - 1) / dw * cfg->n_kv_heads : 0);
   out6[3] = (int32_t)c.ptiles.size() * cfg->n_kv_heads * (c.G / ps::prefill_heads_per_wg(c.G));
   out6[4] = (int32_t)split;
   out6[5] = n_parts;

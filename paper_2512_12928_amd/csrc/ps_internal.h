@@ -11,6 +11,7 @@ constexpr int kHeadDim = 128;
 constexpr int kBlockTokens = 16;
 constexpr int kSliceElems = kBlockTokens * kHeadDim;  // one (block, K|V, kv-head) slice: 4 KiB
 constexpr int kTileTokens = 32;                       // KV tokens per MFMA tile (two blocks)
+constexpr int kMaxGroup = 16;                         // query heads per kv-head
 constexpr int kPartStride = 132;                      // fp32 per split-K partial: o[128], m, l, pad
 constexpr int kClockSlots = 2048;                     // workgroups per role whose clock counters a profiled step records
 
@@ -24,7 +25,14 @@ struct DecodeItem {
   int32_t t1;      // one past the last cached token (kv_len for the final segment)
   int32_t part;    // slot in the partials buffer, or -1: the only segment, write out directly
   int32_t nblk;    // block-table entries of the request
-  int32_t pad[2];
+  int32_t last;    // 1: the request's final segment, the one that holds this step's token
+  int32_t pad;
+};
+
+// A segment that is walked by workgroups of its own (decode_request_kernel), with the block ids of every wave's first tile.
+struct RequestItem {
+  DecodeItem it;
+  int32_t first[8][2];
 };
 
 struct MergeItem {
@@ -87,12 +95,15 @@ struct StepParams {
 // rows (n_items append items, read from aitems_pinned, which lies in the same pinned block).
 hipError_t launch_prologue(const StepParams& p, const void* src_pinned, void* dst, size_t bytes,
                            const AppendItem* aitems_pinned, int n_items, hipStream_t s);
-// merges items [first, first + n_merge) of the merge list
-hipError_t launch_merge(const StepParams& p, int first, int n_merge, hipStream_t s);
+// merges items [first, first + n_merge) of the merge list; longest: partitions of the item that has most
+hipError_t launch_merge(const StepParams& p, int first, int n_merge, int longest, hipStream_t s);
 // One launch for the decode slots and the prefill tiles of the batch (either may be 0).
 // n_decode_wgs_out / n_prefill_wgs_out (may be NULL): the workgroups of each role in the launch.
 hipError_t launch_attention(const StepParams& p, int n_slots, int n_tiles, hipStream_t s, int* n_decode_wgs_out,
                             int* n_prefill_wgs_out);
+// Decode-only batches of few requests: n_items segments (p.ditems points to RequestItems), one workgroup of `waves` (4 or 8) waves per segment
+// and kv-head; append: the step's new K/V rows are written to the cache as well.
+hipError_t launch_decode_requests(const StepParams& p, int n_items, int waves, bool append, hipStream_t s, int* n_wgs_out);
 // The same batch with every workgroup carrying both kinds of work (ps_fused.hip): n_tiles prefill work items as
 // above, whose workgroup bid also walks the decode slots (bid / Hkv) * 3 + 0..2 for kv-head bid % Hkv, so
 // n_slots <= fused_decode_slots(n_tiles, G).  Needs fused_supports(G).

@@ -292,25 +292,232 @@ __device__ __forceinline__ void decode_role(const StepParams& P, const DecodeIte
   if (wg < kClockSlots) clock_record(P, wg, 2);
 }
 
+// ------------------------------------------------------------------------------------ decode, one request per workgroup
+// Decode-only batches of few requests, latency-bound: a workgroup of NW waves owns KV tokens [t0, t1) of ONE request for
+// one kv-head, its waves take an equal share of the range's 32-token tiles each and meet once, at the end, in LDS.  A
+// request that one workgroup can walk in the time the launch takes anyway then needs no partials in memory and no merge
+// launch; with APPEND the wave that holds the request's last tile also takes this step's K/V row from k_new / v_new
+// (into its operand registers) and writes it to the cache, so that a layer is this one launch.
+//   grid: n_items * Hkv workgroups, item = id / Hkv, kv-head = id % Hkv.
+// 16x16x32 MFMA (the G query heads of the kv-head in 16 columns, operand order as in the decode waves of fused_kernel):
+// 32 accumulators and 16 registers of Q leave room for two tiles of K and V in registers, so a wave always has the
+// next tile's 16 loads in flight while it works on one.
+template <int NW, bool APPEND>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_request_kernel(
+    StepParams P, const RequestItem* __restrict__ ritems, const int32_t* __restrict__ block_ids) {
+  __shared__ __attribute__((aligned(16))) float part[NW][kMaxGroup][kPartStride];
+  __shared__ NewRow new_row;
+  hand_back_slot(P);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int Hkv = P.Hkv, G = P.G;
+  const int g = (int)blockIdx.x % Hkv;
+  // the item and the block ids of this wave's first tile, in one round trip to memory
+  const RequestItem* ri = ritems + (int)blockIdx.x / Hkv;
+  const DecodeItem it = ri->it;
+  int nextA = ri->first[wave][0], nextB = ri->first[wave][1];
+  if ((int)blockIdx.x < kClockSlots) clock_record(P, blockIdx.x, 0);
+  const int i = lane & 15;   // row of the K operand / dim row of the V operand / query-head column of Q, P, O
+  const int kg = lane >> 4;  // k-group of the MFMA operands
+  const int k_off = kg * (kBlockTokens * 8) + (8 * ((i >> 2) & 1) + (i & 3)) * 8;  // T0; T1: + 4 slots; chunk c: + 4c groups
+  const bool k_in_b = i >= 8;
+  const int v_off = i * kBlockTokens + 8 * (kg & 1);  // + 16n dims
+  const bool v_in_b = kg >= 2;
+  const int n_tiles = (it.t1 - it.t0 + kTileTokens - 1) / kTileTokens;
+  const int tile0 = n_tiles * wave / NW, tile1 = n_tiles * (wave + 1) / NW;  // this wave's tiles; may be none
+  const int32_t* table = block_ids + it.bt_off;
+
+  float m = PS_NEG_INF, l = 0.f;
+  f32x4 acc[8];
+#pragma unroll
+  for (int n = 0; n < 8; ++n) acc[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  if (tile0 < tile1) {
+    struct Tile {
+      bf16x8 k[2][4], v[8];
+    };
+    // block ids of a tile (an absent second block repeats the first and is masked by the token test), one tile ahead
+    auto tile_ids = [&](int ti) {
+      int bA = (it.t0 >> 4) + 2 * ti;
+      bA = bA < it.nblk ? bA : it.nblk - 1;  // past the last tile: any entry
+      nextA = table[bA];
+      nextB = table[bA + 1 < it.nblk ? bA + 1 : bA];
+    };
+    auto fetch = [&](Tile& t, int ti) {
+      const int idA = nextA, idB = nextB;
+      tile_ids(ti + 1);
+      const uint16_t* kp = k_slice(P.cache, k_in_b ? idB : idA, Hkv, g) + k_off;
+      const uint16_t* vp = v_slice(P.cache, v_in_b ? idB : idA, Hkv, g) + v_off;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        t.k[0][c] = load_stream16(kp + c * 4 * (kBlockTokens * 8));
+        t.k[1][c] = load_stream16(kp + c * 4 * (kBlockTokens * 8) + 4 * 8);
+      }
+#pragma unroll
+      for (int n = 0; n < 8; ++n) t.v[n] = load_stream16(vp + n * 16 * kBlockTokens);
+      __builtin_amdgcn_sched_barrier(0);  // all 16 loads are in flight before anything waits
+    };
+    // Q^T operand: lane (head i, k-group kg) holds dims 32c + 8kg .. +7 for chunk c; columns G..15 repeat head g*G
+    bf16x8 qop[4];
+    {
+      const uint16_t* qrow = P.q + ((size_t)it.tok * P.Hq + g * G + (i < G ? i : 0)) * kHeadDim + kg * 8;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) qop[c] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qrow + c * 32));
+    }
+    // this step's row: wanted by the wave that holds the request's last tile only, requested by all
+    uint32_t k_row = 0, v_row = 0;
+    if (APPEND) load_new_row(P, it.tok, g, lane, k_row, v_row);
+    auto work = [&](Tile& t, int ti, auto last_tag) {
+      constexpr bool LAST = decltype(last_tag)::value;
+      const int ts = it.t0 + ti * kTileTokens;
+      if (APPEND && LAST && it.last && tile1 == n_tiles) {  // wave-uniform
+        const int at = it.t1 - 1 - ts;  // the new token's place in the tile
+        stage_new_row(new_row, lane, k_row, v_row);
+        const int krow = (k_in_b ? 16 : 0) + 8 * ((i >> 2) & 1) + (i & 3);  // T0's token of this lane
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if (krow + 4 * h == at) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) t.k[h][c] = as_bf16x8(*(const uint4*)&new_row.k[16 * c + 4 * kg]);
+          }
+        if (8 * kg <= at && at < 8 * kg + 8) {
+#pragma unroll
+          for (int n = 0; n < 8; ++n) t.v[n] = put8(t.v[n], at & 7, ((const uint16_t*)new_row.v)[16 * n + i]);
+        }
+      }
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.k[0][c], qop[c], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.k[1][c], qop[c], s1, 0, 0, 0);
+      }
+      // s0[e]: token ts + 8kg + e, s1[e]: token ts + 8kg + 4 + e, head i
+      float tmax = PS_NEG_INF;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int tok = ts + 8 * kg + e;
+        s0[e] = (!LAST || tok < it.t1) ? s0[e] * P.scale_log2 : PS_NEG_INF;  // only the last tile is ragged
+        s1[e] = (!LAST || tok + 4 < it.t1) ? s1[e] * P.scale_log2 : PS_NEG_INF;
+        tmax = fmaxf(tmax, fmaxf(s0[e], s1[e]));
+      }
+      if (LAST) {  // slots past the segment's end may hold anything
+#pragma unroll
+        for (int n = 0; n < 8; ++n) t.v[n] = zero_from8(t.v[n], ts + 8 * kg, it.t1);
+      }
+      tmax = xor32_max(xor16_max(tmax));
+      const float m_new = fmaxf(m, tmax);  // finite: every tile holds at least one valid token
+      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0[e] = __builtin_amdgcn_exp2f(s0[e] - m_new);
+        s1[e] = __builtin_amdgcn_exp2f(s1[e] - m_new);
+      }
+      const uint4 pv = {pack_bf16x2(s0[0], s0[1]), pack_bf16x2(s0[2], s0[3]), pack_bf16x2(s1[0], s1[1]), pack_bf16x2(s1[2], s1[3])};
+      l = l * alpha + sum_bf16x8(pv);  // of the rounded probabilities, the ones the output MFMAs multiply by
+      m = m_new;
+#pragma unroll
+      for (int n = 0; n < 8; ++n) acc[n] *= alpha;
+      const bf16x8 pop = as_bf16x8(pv);
+#pragma unroll
+      for (int n = 0; n < 8; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.v[n], pop, acc[n], 0, 0, 0);
+    };
+    // Two tiles in registers: the next tile is requested ahead of the work on this one.  No exit from the middle of the
+    // loop, and the last tile outside it: a wait that has to hold on both sides of a branch around loads becomes a wait
+    // for all of them.
+    Tile ta, tb;
+    int ti = tile0;
+    fetch(ta, ti);
+    for (; ti + 2 < tile1; ti += 2) {
+      fetch(tb, ti + 1);
+      work(ta, ti, std::false_type{});
+      fetch(ta, ti + 2);
+      work(tb, ti + 1, std::false_type{});
+    }
+    if (ti + 1 < tile1) {
+      fetch(tb, ti + 1);
+      work(ta, ti, std::false_type{});
+      work(tb, ti + 1, std::true_type{});
+    } else {
+      work(ta, ti, std::true_type{});
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (APPEND && it.last && tile1 == n_tiles)
+      write_new_row(P, new_row, table[(it.t1 - 1) >> 4], (it.t1 - 1) & (kBlockTokens - 1), g, lane);
+  }
+  // acc[n][e] is dim 16n + 4kg + e of head i
+  if (i < G) {
+#pragma unroll
+    for (int n = 0; n < 8; ++n) *(f32x4*)&part[wave][i][16 * n + 4 * kg] = acc[n];
+    if (kg == 0) {
+      part[wave][i][128] = m;
+      part[wave][i][129] = l;
+    }
+  }
+  __syncthreads();
+  // 32 threads per head, 4 dims each
+  for (int h = threadIdx.x >> 5; h < G; h += NW * 2) {
+    const int x = (threadIdx.x & 31) * 4;
+    float mw[NW], ms = PS_NEG_INF, L = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      mw[w] = part[w][h][128];
+      ms = fmaxf(ms, mw[w]);
+    }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float f = __builtin_amdgcn_exp2f(mw[w] - ms);  // 0 for a wave without tiles (m = -inf): ms is finite
+      L += part[w][h][129] * f;
+      o += *(const f32x4*)&part[w][h][x] * f;
+    }
+    const int head = g * G + h;
+    if (it.part < 0) {
+      o *= 1.f / L;
+      const size_t ob = ((size_t)it.tok * P.Hq + head) * kHeadDim + x;
+      if (P.out_f32) {
+        *(f32x4*)((float*)P.out + ob) = o;
+      } else {
+        uint2 w2 = {pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+        *(uint2*)((uint16_t*)P.out + ob) = w2;
+      }
+    } else {  // unnormalised partial for the merge kernel
+      float* dst = P.partials + ((size_t)it.part * P.Hq + head) * kPartStride;
+      *(f32x4*)(dst + x) = o;
+      if (x == 0) {
+        dst[128] = ms;
+        dst[129] = L;
+      }
+    }
+  }
+  if ((int)blockIdx.x < kClockSlots) clock_record(P, blockIdx.x, 2);
+}
+
 // Combines the split-K partials of one token (decode, or a prefill row whose KV range was split).
-// grid (n_merge, ceil(Hq/8)), 256 threads: 32 lanes per (token, head), 4 dims per lane.  The
-// partials of up to 8 partitions are loaded at once (nothing but the item is on their address
-// path); longer lists are folded in 8 at a time with a running maximum.
+// 256 threads: eight groups of 32 lanes, 4 dims per lane.  LONG = false, grid (n_merge, ceil(Hq/8)): a group per head, all
+// partials of up to 8 partitions in flight at once (nothing but the item is on their address path), longer lists 8 at a
+// time with a running maximum.  LONG = true, grid (n_merge, Hq): all eight groups on one head, every eighth partition
+// each, and one meeting in LDS -- for launches with a list of more than 8 (a request of 32 k tokens alone has 128
+// partials: 16 trips to memory one after the other otherwise, 9 us more).
+template <bool LONG>
 __global__ __launch_bounds__(256) void merge_kernel(StepParams P, int first) {
+  __shared__ __attribute__((aligned(16))) float meet[LONG ? 8 : 1][kPartStride];
   const MergeItem it = P.mitems[first + blockIdx.x];
-  const int head = blockIdx.y * 8 + (threadIdx.x >> 5);
+  const int group = threadIdx.x >> 5;
+  const int head = LONG ? (int)blockIdx.y : (int)blockIdx.y * 8 + group;
   if (head >= P.Hq) return;
+  const int k_first = LONG ? group : 0, k_step = LONG ? 8 : 1;
   const int x = (threadIdx.x & 31) * 4;
   const float* base = P.partials + ((size_t)it.part0 * P.Hq + head) * kPartStride;
   const size_t stride = (size_t)P.Hq * kPartStride;
   float mstar = PS_NEG_INF, L = 0.f;
   f32x4 o = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < it.n_parts; k0 += 8) {
+  for (int k0 = k_first; k0 < it.n_parts; k0 += 8 * k_step) {
     float mk[8], lk[8];
     f32x4 ok[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int k = k0 + i < it.n_parts ? k0 + i : it.n_parts - 1;
+      const int k = k0 + i * k_step < it.n_parts ? k0 + i * k_step : it.n_parts - 1;
       const float* p = base + (size_t)k * stride;
       mk[i] = p[128];
       lk[i] = p[129];
@@ -319,7 +526,7 @@ __global__ __launch_bounds__(256) void merge_kernel(StepParams P, int first) {
     float m_new = mstar;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      if (k0 + i >= it.n_parts) mk[i] = PS_NEG_INF;  // a repeat of the last partition: weight 0
+      if (k0 + i * k_step >= it.n_parts) mk[i] = PS_NEG_INF;  // a repeat of the last partition: weight 0
       m_new = fmaxf(m_new, mk[i]);
     }
     // a partition whose row saw no key has m = -inf (and l = 0, o = 0): weight 0
@@ -333,6 +540,26 @@ __global__ __launch_bounds__(256) void merge_kernel(StepParams P, int first) {
       o += ok[i] * f;
     }
     mstar = m_new;
+  }
+  if (LONG) {
+    *(f32x4*)&meet[group][x] = o;
+    if (x == 0) {
+      meet[group][128] = mstar;
+      meet[group][129] = L;
+    }
+    __syncthreads();
+    if (group != 0) return;
+    mstar = PS_NEG_INF;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mstar = fmaxf(mstar, meet[i][128]);
+    L = 0.f;
+    o = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float f = meet[i][128] == PS_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(meet[i][128] - mstar);
+      L += meet[i][129] * f;
+      o += *(const f32x4*)&meet[i][x] * f;
+    }
   }
   const size_t oi = ((size_t)it.tok * P.Hq + head) * kHeadDim + x;
   const float inv = 1.f / L;
@@ -721,9 +948,12 @@ hipError_t launch_prologue(const StepParams& p, const void* src_pinned, void* ds
   return hipGetLastError();
 }
 
-hipError_t launch_merge(const StepParams& p, int first, int n_merge, hipStream_t s) {
+hipError_t launch_merge(const StepParams& p, int first, int n_merge, int longest, hipStream_t s) {
   if (n_merge <= 0) return hipSuccess;
-  hipLaunchKernelGGL(merge_kernel, dim3(n_merge, (p.Hq + 7) / 8), dim3(256), 0, s, p, first);
+  if (longest > 8)
+    hipLaunchKernelGGL((merge_kernel<true>), dim3(n_merge, p.Hq), dim3(256), 0, s, p, first);
+  else
+    hipLaunchKernelGGL((merge_kernel<false>), dim3(n_merge, (p.Hq + 7) / 8), dim3(256), 0, s, p, first);
   return hipGetLastError();
 }
 
@@ -746,6 +976,26 @@ hipError_t launch_attention(const StepParams& p, int n_slots, int n_tiles, hipSt
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL(attention_kernel, dim3((unsigned)grid), dim3(kPrefillWaves * 64), 0, s, p, p.ditems, p.dslots, p.block_ids,
                      n_slots, (int)n_decode_wgs, HW, nz);
+  return hipGetLastError();
+}
+
+hipError_t launch_decode_requests(const StepParams& p, int n_items, int waves, bool append, hipStream_t s, int* n_wgs_out) {
+  const long long grid = (long long)n_items * p.Hkv;
+  if (n_wgs_out) *n_wgs_out = (int)std::min<long long>(grid, 0x7fffffffLL);
+  if (grid <= 0) return hipSuccess;
+  if (grid > 0x7fffffffLL || p.G > kMaxGroup) return hipErrorInvalidValue;
+  const dim3 gr((unsigned)grid), bl(waves * 64);
+  const RequestItem* ritems = (const RequestItem*)p.ditems;
+  if (waves == 8 && append)
+    hipLaunchKernelGGL((decode_request_kernel<8, true>), gr, bl, 0, s, p, ritems, p.block_ids);
+  else if (waves == 8)
+    hipLaunchKernelGGL((decode_request_kernel<8, false>), gr, bl, 0, s, p, ritems, p.block_ids);
+  else if (waves == 4 && append)
+    hipLaunchKernelGGL((decode_request_kernel<4, true>), gr, bl, 0, s, p, ritems, p.block_ids);
+  else if (waves == 4)
+    hipLaunchKernelGGL((decode_request_kernel<4, false>), gr, bl, 0, s, p, ritems, p.block_ids);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

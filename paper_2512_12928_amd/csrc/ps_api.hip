@@ -1546,7 +1546,7 @@ static int swap_common(ps_ctx* c, bool out_dir, const int32_t* dev_ids, const in
     const size_t bb = c->block_bytes;
     char* hp = (char*)const_cast<void*>(host_pool);
     if (out_dir) {
-      PS_HIP(ps::launch_block_copy(d, d + 2 * m, m, kv_cache, st.dev, bb, 64, stream));
+      PS_HIP(ps::launch_block_copy(d, d + 2 * m, m, kv_cache, st.dev, bb, 64, false, stream));
       for (int k0 = 0; k0 < m;) {
         int k1 = k0 + 1;
         while (k1 < m && host_ids[k1] == host_ids[k1 - 1] + 1) ++k1;
@@ -1562,18 +1562,17 @@ static int swap_common(ps_ctx* c, bool out_dir, const int32_t* dev_ids, const in
                               hipMemcpyHostToDevice, stream));
         k0 = k1;
       }
-      PS_HIP(ps::launch_block_copy(d + 2 * m, d, m, st.dev, const_cast<void*>(kv_cache), bb, 64, stream));
+      PS_HIP(ps::launch_block_copy(d + 2 * m, d, m, st.dev, const_cast<void*>(kv_cache), bb, 64, false, stream));
     }
     PS_HIP(hipEventRecord(st.done, stream));
     st.last_stream = stream;
     st.used = true;
   } else {
-    // measured next to a running attention step: 8 workgroups move more than 32 or 128 do
-    const int wgs = c->cfg.swap_workgroups > 0 ? c->cfg.swap_workgroups : 8;
+    const int wgs = c->cfg.swap_workgroups;
     if (out_dir)
-      PS_HIP(ps::launch_block_copy(d, d + m, m, kv_cache, const_cast<void*>(host_pool), c->block_bytes, wgs, stream));
+      PS_HIP(ps::launch_block_copy(d, d + m, m, kv_cache, const_cast<void*>(host_pool), c->block_bytes, wgs, true, stream));
     else
-      PS_HIP(ps::launch_block_copy(d + m, d, m, host_pool, const_cast<void*>(kv_cache), c->block_bytes, wgs, stream));
+      PS_HIP(ps::launch_block_copy(d + m, d, m, host_pool, const_cast<void*>(kv_cache), c->block_bytes, wgs, false, stream));
   }
   // the call's event: its ticket, and the end of the id list's use (a swap slot is used again long before the event is)
   const uint64_t id = c->next_ticket++;

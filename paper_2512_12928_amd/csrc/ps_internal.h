@@ -116,6 +116,6 @@ int decode_waves_per_wg();
 int prefill_tile_tokens(int G);
 int prefill_heads_per_wg(int G);
 hipError_t launch_block_copy(const int32_t* src_ids, const int32_t* dst_ids, int n, const void* src_pool,
-                             void* dst_pool, size_t block_bytes, int workgroups, hipStream_t s);
+                             void* dst_pool, size_t block_bytes, int workgroups, bool to_host, hipStream_t s);
 
 }  // namespace ps

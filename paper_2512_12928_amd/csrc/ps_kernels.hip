@@ -914,24 +914,39 @@ __global__ __launch_bounds__(kPrefillWaves * 64) void attention_kernel(StepParam
 // pass (LPL 16-byte loads in flight per lane, then LPL stores); grid-stride over units.  Few
 // workgroups with many loads in flight each: next to an attention kernel that saturates HBM the
 // copy's own read latency grows several-fold, and it is bytes in flight that keep the link busy.
-template <int LPL>
+// THROUGH: the stores are written through the L2 at once (device scope).  Towards host memory that is what lets both
+// directions run side by side: with stores that the L2 drains when it pleases, reads of host memory next to them take
+// turns with bursts of writes (512 blocks each way: 1030 us, written through 800, with the ids prefetched 754).
+template <int LPL, bool THROUGH>
 __global__ __launch_bounds__(256) void block_copy_kernel(const int32_t* __restrict__ src_ids,
                                                          const int32_t* __restrict__ dst_ids, int n,
                                                          const char* __restrict__ src_pool,
                                                          char* __restrict__ dst_pool, size_t block_bytes) {
   constexpr size_t kUnit = (size_t)LPL * 4096;
   const int upb = (int)(block_bytes / kUnit);
-  const long total = (long)n * upb;
-  for (long u = blockIdx.x; u < total; u += gridDim.x) {
-    const int k = (int)(u / upb);
+  const int total = n * upb, stride = (int)gridDim.x;
+  // the id lists lie in pinned host memory too: the next unit's ids are fetched while this one's data is under way
+  int src_id = src_ids[(int)blockIdx.x / upb], dst_id = dst_ids[(int)blockIdx.x / upb];
+  for (int u = blockIdx.x; u < total; u += stride) {
     const size_t off = (size_t)(u % upb) * kUnit + threadIdx.x * 16;
-    const char* s = src_pool + (size_t)src_ids[k] * block_bytes + off;
-    char* d = dst_pool + (size_t)dst_ids[k] * block_bytes + off;
+    const char* s = src_pool + (size_t)src_id * block_bytes + off;
+    char* d = dst_pool + (size_t)dst_id * block_bytes + off;
+    const int next = (u + stride < total ? u + stride : u) / upb;
+    src_id = src_ids[next];
+    dst_id = dst_ids[next];
     u32x4 v[LPL];
 #pragma unroll
     for (int i = 0; i < LPL; ++i) v[i] = __builtin_nontemporal_load((const u32x4*)(s + i * 4096));
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < LPL; ++i) __builtin_nontemporal_store(v[i], (u32x4*)(d + i * 4096));
+    for (int i = 0; i < LPL; ++i) {
+      if (THROUGH)
+        // the no-op: a vector write to a store's data registers has to keep one wait state away from a 16-byte store, and
+        // the compiler does not look into the asm for that
+        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(d + i * 4096), "v"(v[i]) : "memory");
+      else
+        __builtin_nontemporal_store(v[i], (u32x4*)(d + i * 4096));
+    }
   }
 }
 
@@ -950,7 +965,8 @@ hipError_t launch_prologue(const StepParams& p, const void* src_pinned, void* ds
 
 hipError_t launch_merge(const StepParams& p, int first, int n_merge, int longest, hipStream_t s) {
   if (n_merge <= 0) return hipSuccess;
-  if (longest > 8)
+  // eight times the workgroups: worth it where the lists are long and few, not where the launch fills the chip anyway
+  if (longest > 8 && (long long)n_merge * p.Hq <= 4096)
     hipLaunchKernelGGL((merge_kernel<true>), dim3(n_merge, p.Hq), dim3(256), 0, s, p, first);
   else
     hipLaunchKernelGGL((merge_kernel<false>), dim3(n_merge, (p.Hq + 7) / 8), dim3(256), 0, s, p, first);
@@ -999,19 +1015,31 @@ hipError_t launch_decode_requests(const StepParams& p, int n_items, int waves, b
   return hipGetLastError();
 }
 
+// workgroups 0: picked here, 512 KiB in flight per direction (eight blocks of 64 KiB).  512 blocks of 64 KiB, us with
+// workgroups out x in: out alone, in alone, both ways at once, both next to a mixed step of 268 us: 3 x 6 603, 618, 717,
+// 755; 6 x 6 596, 617, 761, 812; 8 x 8 606, 600, 754, 762; 4 x 8 598, 600, 853, 817.  (The link alone would take 590
+// either way; the copy engines 700 for both, but a DMA call per block costs 10 us each.)
 hipError_t launch_block_copy(const int32_t* src_ids, const int32_t* dst_ids, int n, const void* src_pool,
-                             void* dst_pool, size_t block_bytes, int workgroups, hipStream_t s) {
+                             void* dst_pool, size_t block_bytes, int workgroups, bool to_host, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const bool big = block_bytes % 32768 == 0;  // else a block is an odd multiple of 8 KiB
-  const long total = (long)n * (long)(block_bytes / (big ? 32768 : 8192));
-  int grid = (int)(total < workgroups ? total : workgroups);
-  if (grid < 1) grid = 1;
-  if (big)
-    hipLaunchKernelGGL(block_copy_kernel<8>, dim3(grid), dim3(256), 0, s, src_ids, dst_ids, n,
-                       (const char*)src_pool, (char*)dst_pool, block_bytes);
-  else
-    hipLaunchKernelGGL(block_copy_kernel<2>, dim3(grid), dim3(256), 0, s, src_ids, dst_ids, n,
-                       (const char*)src_pool, (char*)dst_pool, block_bytes);
+  int lpl = 16;  // one block per pass where a block is 64 KiB; 2 for an odd multiple of 8 KiB
+  while (block_bytes % ((size_t)lpl * 4096) != 0) lpl /= 2;
+  if (workgroups <= 0) workgroups = 8 * (16 / lpl);
+  const long total = (long)n * (long)(block_bytes / (size_t)(lpl * 4096));
+  if (total > 0x3fffffffL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)std::max(1L, std::min(total, (long)workgroups))), block(256);
+  const char* src = (const char*)src_pool;
+  char* dst = (char*)dst_pool;
+#define PS_COPY(LPL, THROUGH) hipLaunchKernelGGL((block_copy_kernel<LPL, THROUGH>), grid, block, 0, s, src_ids, dst_ids, n, src, dst, block_bytes)
+  if (lpl == 16 && to_host) PS_COPY(16, true);
+  else if (lpl == 16) PS_COPY(16, false);
+  else if (lpl == 8 && to_host) PS_COPY(8, true);
+  else if (lpl == 8) PS_COPY(8, false);
+  else if (lpl == 4 && to_host) PS_COPY(4, true);
+  else if (lpl == 4) PS_COPY(4, false);
+  else if (to_host) PS_COPY(2, true);
+  else PS_COPY(2, false);
+#undef PS_COPY
   return hipGetLastError();
 }
 

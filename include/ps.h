@@ -244,7 +244,8 @@ int ps_plan_decode(const ps_layer_cfg* cfg, const ps_batch* batch, int32_t waves
  *   out6[0] decode waves     out6[1] decode slots (waves / Hkv); laid out by request: segments, and workgroups
  *   out6[2] decode workgroups (four slots each; laid out by request, one segment each); 0 for a mixed batch whose workgroups carry both kinds of work (cfg.mixed_launch):
  *           then every prefill workgroup also walks up to two of the decode slots
- *   out6[3] prefill workgroups     out6[4] KV tiles (64 tokens) per partition of split prefill rows, 0 = no row split
+ *   out6[3] prefill workgroups (where they fill at most half of the units, two workgroups share the work of each)
+ *   out6[4] KV tiles (64 tokens) per partition of split prefill rows, 0 = no row split
  *   out6[5] split-K partial slots the step uses
  * Errors as for ps_step's validation. */
 int ps_plan_launch(const ps_layer_cfg* cfg, const ps_batch* batch, int32_t n_cus, int32_t* out6);

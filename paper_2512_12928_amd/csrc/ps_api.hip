@@ -85,6 +85,7 @@ struct DecodePlan {
   std::vector<double> bins;
   std::vector<ps::RequestItem> ritems;  // what goes to the device in the place of ditems if request_waves > 0
   int longest_merge = 0;                // partitions of the merge item that has most
+  int prefill_ks = 1;     // workgroups per prefill work item
   int request_waves = 0;  // > 0: every item is walked by workgroups of its own, of this many waves (decode_request_kernel)
 };
 
@@ -215,12 +216,18 @@ static int64_t prefill_partial_budget(int64_t n_tokens) {
   return std::min<int64_t>((int64_t)kMaxPrefillParts * n_tokens, 2 * n_tokens + 8192);
 }
 
-double plan_prefill(ps_ctx* c, const ps_batch* b, std::vector<TileKey>& tiles, int TT, size_t workspace_bytes, int& n_parts) {
+double plan_prefill(ps_ctx* c, const ps_batch* b, std::vector<TileKey>& tiles, int TT, size_t workspace_bytes, double t_d, int& n_parts) {
   double prefill_steps = 0;
   const PlanTuning tune = tuning_of(c->cfg);
-  const int wg_per_tile = c->cfg.n_kv_heads * (c->G / ps::prefill_heads_per_wg(c->G));
   int64_t longest = 0;
   for (auto& t : tiles) longest = std::max(longest, t.reach);
+  // t_d: time of the batch's decode work, 0 if it has none
+  const bool may_halve = c->cfg.mixed_launch != 2 && (t_d == 0 || c->cfg.decode_waves == 0);
+  const auto halved = [&](int64_t wgs, double steps) {  // room for two workgroups per item, next to the decode work's units
+    const int decode_units = t_d > 0 ? std::max(8, (int)(tune.decode_share * c->n_cus * t_d / (t_d + steps * tune.tile_step_us))) : 0;
+    return may_halve && longest > 1 && wgs * 2 + decode_units <= c->n_cus;
+  };
+  const int wg_per_tile = c->cfg.n_kv_heads * (c->G / ps::prefill_heads_per_wg(c->G));
   int64_t split = 0;  // partition length in KV tiles; 0 = none
   bool priced = false;
   {  // default price of the prefill work, in KV tile steps per CU: an even spread
@@ -236,11 +243,16 @@ double plan_prefill(ps_ctx* c, const ps_batch* b, std::vector<TileKey>& tiles, i
     // ends when workgroups are handed, longest first, to whichever CU is free next, plus the merge
     // (a kernel launch worth 4 steps, and 0.0047 steps per partial row of 32 heads).  Launches of
     // more than 1024 workgroups balance well enough without a cut and are not priced.
+    // Where a candidate leaves half of the units that the decode work does not take without a workgroup, its items are
+    // walked by two workgroups each (prefill_role's KS = 2), in tile steps of 0.62: measured with 32/8 heads, a chunk of
+    // 256 first tokens 21.5 -> 19.5 us, 512 28.3 -> 24.1, 1024 41.3 -> 33.6; 512 behind 512 40.5 -> 32.7.  With more
+    // workgroups than units it is the loser (4096 first tokens 148 -> 181), with walks of one tile it gains nothing.
+    // Walks are then cut down to 4 tiles instead of 8 (512 behind 3584 71.6 -> 57.4).
     std::vector<int64_t> sizes, bins;
     double best = 0;
     for (int k : {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32}) {
       const int64_t cand = (longest + k - 1) / k;
-      if (k > 1 && cand < 8) break;
+      if (k > 1 && cand < 4) break;
       sizes.clear();
       int64_t rows = 0;
       for (auto& t : tiles) {
@@ -250,7 +262,8 @@ double plan_prefill(ps_ctx* c, const ps_batch* b, std::vector<TileKey>& tiles, i
         for (int q = 0; q < np; ++q) sizes.push_back(std::min<int64_t>((int64_t)(q + 1) * len, t.reach) - q * len);
         if (np > 1) rows += (int64_t)std::min(TT, b->q_start[t.t.req + 1] - b->q_start[t.t.req] - t.t.q0) * np;
       }
-      if (sizes.size() * (size_t)wg_per_tile > 1024) break;
+      const int64_t wgs = (int64_t)sizes.size() * wg_per_tile;
+      if (wgs > 1024 || (k > 1 && cand < 8 && (!may_halve || wgs * 2 > c->n_cus))) break;
       std::sort(sizes.begin(), sizes.end(), std::greater<int64_t>());
       bins.assign((size_t)c->n_cus, 0);  // min-heap of CU finish times
       auto later = std::greater<int64_t>();
@@ -261,7 +274,11 @@ double plan_prefill(ps_ctx* c, const ps_batch* b, std::vector<TileKey>& tiles, i
           std::push_heap(bins.begin(), bins.end(), later);
         }
       const int64_t makespan = *std::max_element(bins.begin(), bins.end());
-      const double cost = (double)makespan + (rows > 0 ? tune.merge_launch_steps : 0.0) +
+      constexpr double kHalfStep = 0.62;
+      const double steps = (double)makespan * kHalfStep;
+      const bool twice = halved(wgs, steps);
+      if (k > 1 && cand < 8 && !twice) break;
+      const double cost = (twice ? steps : (double)makespan) + (rows > 0 ? tune.merge_launch_steps : 0.0) +
                           tune.merge_row_steps * (c->cfg.n_q_heads / 32.0) * (double)rows;
       if (k == 1 || cost < best) {
         best = cost;
@@ -314,6 +331,7 @@ double plan_prefill(ps_ctx* c, const ps_batch* b, std::vector<TileKey>& tiles, i
     prefill_steps = std::max(prefill_steps, (double)longest_part) + (rows > 0 ? tune.merge_launch_steps : 0.0) +
                     tune.merge_row_steps * (c->cfg.n_q_heads / 32.0) * (double)rows;
   }
+  c->plan.prefill_ks = halved((int64_t)tiles.size() * wg_per_tile, prefill_steps) ? 2 : 1;
   return prefill_steps;
 }
 
@@ -1044,7 +1062,9 @@ static int plan_batch(ps_ctx* c, const ps_batch* b, bool has_new_kv, size_t work
       }
     }
   }
-  const double prefill_steps = plan_prefill(c, b, tiles, TT, workspace_bytes, n_parts);
+  const PlanTuning tune = tuning_of(c->cfg);
+  const double t_d = (double)decode_kv * (double)(c->block_bytes / ps::kBlockTokens) / (tune.stream_TBps * 1e6);  // us of decode work
+  const double prefill_steps = plan_prefill(c, b, tiles, TT, workspace_bytes, t_d, n_parts);
   // launch order of the prefill work items: heaviest partitions first, so the tail of the launch is made of short ones
   std::stable_sort(tiles.begin(), tiles.end(), [](const TileKey& a, const TileKey& b2) { return a.reach > b2.reach; });
 
@@ -1070,8 +1090,6 @@ static int plan_batch(ps_ctx* c, const ps_batch* b, bool has_new_kv, size_t work
                          (int64_t)ps::fused_decode_slots((int)tiles.size(), c->G) * c->cfg.n_kv_heads <= INT32_MAX;
     c->plan_fused = fusable && c->cfg.mixed_launch == 2;
     if (fusable && c->cfg.mixed_launch == 0) {
-      const PlanTuning tune = tuning_of(c->cfg);
-      const double t_d = (double)decode_kv * (double)(c->block_bytes / ps::kBlockTokens) / (tune.stream_TBps * 1e6);  // us
       const double t_p = prefill_steps * tune.tile_step_us;
       const int64_t wgs = (int64_t)tiles.size() * c->cfg.n_kv_heads * (c->G / ps::prefill_heads_per_wg(c->G));
       int64_t walk_sum = 0;
@@ -1082,8 +1100,6 @@ static int plan_batch(ps_ctx* c, const ps_batch* b, bool has_new_kv, size_t work
     if (c->plan_fused) {
       waves = ps::fused_decode_slots((int)tiles.size(), c->G) * c->cfg.n_kv_heads;
     } else if (c->cfg.decode_waves == 0 && c->profiling != 2 && !decode_reqs.empty() && !tiles.empty()) {
-      const PlanTuning tune = tuning_of(c->cfg);
-      const double t_d = (double)decode_kv * (double)(c->block_bytes / ps::kBlockTokens) / (tune.stream_TBps * 1e6);  // us
       const double t_p = prefill_steps * tune.tile_step_us;
       const int lo = std::min(8, c->n_cus), hi = c->n_cus - 8;
       int cus = (int)(tune.decode_share * c->n_cus * t_d / (t_d + t_p));
@@ -1121,7 +1137,7 @@ static int plan_batch(ps_ctx* c, const ps_batch* b, bool has_new_kv, size_t work
       std::vector<int64_t> weight((size_t)per_item * tiles.size());
       for (size_t x = 0; x < weight.size(); ++x) weight[x] = tiles[x / (size_t)per_item].reach;
       build_weighted_decode_slots(&c->plan, b, decode_reqs, n_parts, weight);
-    } else if (c->cfg.decode_chunk == 0 && c->cfg.decode_waves == 0 && tiles.empty() && build_decode_requests(&c->plan, b, decode_reqs, n_parts, c->cfg.n_kv_heads, c->n_cus, tuning_of(c->cfg).stream_TBps)) {
+    } else if (c->cfg.decode_chunk == 0 && c->cfg.decode_waves == 0 && tiles.empty() && build_decode_requests(&c->plan, b, decode_reqs, n_parts, c->cfg.n_kv_heads, c->n_cus, tune.stream_TBps)) {
       c->aitems.clear();  // the attention launch appends
     } else {
       build_decode_slots(&c->plan, c->cfg.n_kv_heads, c->cfg.decode_chunk, b, decode_reqs, n_parts, waves);
@@ -1195,9 +1211,9 @@ static int launch_phases(ps_ctx* c, const char* h, size_t upload_bytes, const ps
   // disjoint CUs).  Profiling mode 2 gives each its own launch instead.
   const int n_slots = (int)c->plan.dslots.size() - 1;
   if (prof == 2 && c->plan.request_waves == 0) {
-    PS_HIP(ps::launch_attention(P, n_slots, 0, stream, &c->prof_wgs[0], nullptr));
+    PS_HIP(ps::launch_attention(P, n_slots, 0, 1, stream, &c->prof_wgs[0], nullptr));
     PS_HIP(hipEventRecord(c->prof_ev_now()[3], stream));
-    PS_HIP(ps::launch_attention(P, 0, (int)c->ptiles.size(), stream, nullptr, &c->prof_wgs[1]));
+    PS_HIP(ps::launch_attention(P, 0, (int)c->ptiles.size(), c->plan.prefill_ks, stream, nullptr, &c->prof_wgs[1]));
     PS_HIP(hipEventRecord(c->prof_ev_now()[4], stream));
   } else {
     if (c->plan.request_waves > 0) {
@@ -1207,7 +1223,7 @@ static int launch_phases(ps_ctx* c, const char* h, size_t upload_bytes, const ps
       PS_HIP(ps::launch_fused(P, n_slots, (int)c->ptiles.size(), stream, &c->prof_wgs[1]));
       c->prof_wgs[0] = c->prof_wgs[1];
     } else {
-      PS_HIP(ps::launch_attention(P, n_slots, (int)c->ptiles.size(), stream, &c->prof_wgs[0], &c->prof_wgs[1]));
+      PS_HIP(ps::launch_attention(P, n_slots, (int)c->ptiles.size(), c->plan.prefill_ks, stream, &c->prof_wgs[0], &c->prof_wgs[1]));
     }
     if (prof) {
       PS_HIP(hipEventRecord(c->prof_ev_now()[3], stream));

@@ -98,8 +98,9 @@ hipError_t launch_prologue(const StepParams& p, const void* src_pinned, void* ds
 // merges items [first, first + n_merge) of the merge list; longest: partitions of the item that has most
 hipError_t launch_merge(const StepParams& p, int first, int n_merge, int longest, hipStream_t s);
 // One launch for the decode slots and the prefill tiles of the batch (either may be 0).
+// ks: workgroups per prefill work item (1, or 2 with half of it each, see prefill_role).
 // n_decode_wgs_out / n_prefill_wgs_out (may be NULL): the workgroups of each role in the launch.
-hipError_t launch_attention(const StepParams& p, int n_slots, int n_tiles, hipStream_t s, int* n_decode_wgs_out,
+hipError_t launch_attention(const StepParams& p, int n_slots, int n_tiles, int ks, hipStream_t s, int* n_decode_wgs_out,
                             int* n_prefill_wgs_out);
 // Decode-only batches of few requests: n_items segments (p.ditems points to RequestItems), one workgroup of `waves` (4 or 8) waves per segment
 // and kv-head; append: the step's new K/V rows are written to the cache as well.

@@ -624,24 +624,40 @@ struct PrefillStage {
 };
 
 // bid: index of the prefill workgroup in the launch; sm: the LDS ring of kStages tiles; id_lds: kIdTiles * 4 ints.
-__device__ __forceinline__ void prefill_role(const StepParams& P, int bid, int HW, int n_zsplit, PrefillStage* sm, int* id_lds) {
+//
+// KS = 2, for launches that do not fill the chip: a work item is walked by two workgroups, each with half of its rows (or
+// half of its heads, where an item is 32 rows of eight heads).  Waves w and w + 4 of a workgroup share 32 rows of a head
+// and take one 32-token half of every KV tile each; they meet once, at the end, in LDS.  A tile step takes 0.9 us instead
+// of 1.5 (the same loads and barrier, half the matrix and softmax work per wave) and twice as many units are at work: a
+// first chunk of 512 tokens (32/8 heads: 64 workgroups before) walks its 8 tiles in 7 us instead of 12.
+template <int KS>
+__device__ __forceinline__ void prefill_role(const StepParams& P, int bid, int HW_item, int n_zsplit, PrefillStage* sm, int* id_lds) {
+  static_assert(KS == 1 || KS == 2, "waves that share a wave's rows");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = lane & 31;   // row of the K operand / query column of Q, P, O
   const int h2 = lane >> 5;  // k-group
   const int Hkv = P.Hkv, G = P.G;
   const int g = bid % Hkv;
-  const int z = (bid / Hkv) % n_zsplit;
-  const PrefillTile t = P.ptiles[bid / (Hkv * n_zsplit)];
-  const int head = g * G + z * HW + wave % HW;
-  const int SUB = kPrefillWaves / HW;
+  const int half = KS == 2 ? (bid / Hkv) & 1 : 0;  // of the item
+  const int item = KS == 2 ? bid / Hkv / 2 : bid / Hkv;
+  const int z = item % n_zsplit;
+  PrefillTile t = P.ptiles[item / n_zsplit];
+  const int ks = KS == 2 ? wave >> 2 : 0;           // this wave's half of every KV tile
+  const int wrow = KS == 2 ? wave & 3 : wave;       // its place among the workgroup's (rows, head) pairs
+  const int HW = KS == 2 && HW_item == 8 ? 4 : HW_item;
+  const int SUB = kPrefillWaves / KS / HW;
+  const int head = g * G + z * HW_item + (KS == 2 && HW_item == 8 ? 4 * half : 0) + wrow % HW;
+  const int q_item = t.q0;                          // partial slots count from the item's first row
+  if (KS == 2 && HW_item < 8) t.q0 += half * SUB * kPrefillRows;
   const int r = t.req;
   const int qs = P.q_start[r];
   const int lq = P.q_start[r + 1] - qs;
   const int L = P.kv_len[r];
   const int p = L - lq;
-  const int q0 = t.q0 + (wave / HW) * kPrefillRows;  // this wave's first query token
+  const int q0 = t.q0 + (wrow / HW) * kPrefillRows;  // this wave's first query token
   const bool active = q0 < lq;
+  if (KS == 2 && t.q0 >= lq) return;  // workgroup-uniform: the item's rows end in the first half
   const int* table = P.block_ids + P.bt_start[r];
   const int nblk = (L + kBlockTokens - 1) >> 4;
 
@@ -666,7 +682,7 @@ __device__ __forceinline__ void prefill_role(const StepParams& P, int bid, int H
   const int reach = (p + wg_last) / kPrefillKV + 1;  // KV tiles any query of the workgroup can see
   const int tile0 = t.tile_begin;                    // this partition: tiles [tile0, tile1)
   const int tile1 = t.tile_end < reach ? t.tile_end : reach;
-  const int ntiles = tile1 - tile0;                  // workgroup-uniform; the host never makes it < 1
+  const int ntiles = tile1 - tile0;                  // workgroup-uniform; < 1 only for the first half of an item whose second half alone reaches the partition
   const int nt_ids = ntiles > 1 ? ntiles : 1;        // tiles whose block ids are looked up (never none)
   const int my_last = p + (q0 + kPrefillRows < lq ? q0 + kPrefillRows : lq) - 1;  // last visible key
   const int qpos = p + q0 + j;
@@ -768,20 +784,21 @@ __device__ __forceinline__ void prefill_role(const StepParams& P, int bid, int H
       __syncthreads();  // workgroup-uniform branch
     }
 
-    if (active && ts <= my_last) {
+    if (active && ts + 32 * ks <= my_last) {
+      constexpr int NH = 2 / KS;  // halves of the tile this wave works on: ks, or both
       const PrefillStage& S = sm[stage];
       // all 16 K fragments of the tile are requested from LDS before the first MFMA needs one,
       // and the 16 V fragments right behind them, so that LDS latency is paid once per tile, not
       // once per MFMA (left alone, the compiler sinks every ds_read next to its MFMA)
-      bf16x8 kf[2][8], vf[2][8];
+      bf16x8 kf[NH][8], vf[NH][8];
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf)
+      for (int hf = 0; hf < NH; ++hf)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) kf[hf][c] = as_bf16x8(S.h[hf].k[j >> 4][(2 * c + h2) * 16 + kslot]);
+        for (int c = 0; c < 8; ++c) kf[hf][c] = as_bf16x8(S.h[ks + hf].k[j >> 4][(2 * c + h2) * 16 + kslot]);
       __builtin_amdgcn_sched_barrier(0);
-      f32x16 s[2];
+      f32x16 s[NH];
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
+      for (int hf = 0; hf < NH; ++hf) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[hf][e] = 0.f;
 #pragma unroll
@@ -789,22 +806,23 @@ __device__ __forceinline__ void prefill_role(const StepParams& P, int bid, int H
           s[hf] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[hf][c], qop[c], s[hf], 0, 0, 0);
       }
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf)
+      for (int hf = 0; hf < NH; ++hf)
 #pragma unroll
-        for (int f = 0; f < 8; ++f) vf[hf][f] = as_bf16x8(S.h[hf].v[f][lane]);
+        for (int f = 0; f < 8; ++f) vf[hf][f] = as_bf16x8(S.h[ks + hf].v[f][lane]);
       __builtin_amdgcn_sched_barrier(0);
       // s[hf][e]: token ts + 32*hf + 16*(e/8) + 8*h2 + e%8, query q0 + j (raw dot products)
       if (ts + kPrefillKV - 1 > p + q0) {  // diagonal tile (wave-uniform test)
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
+        for (int hf = 0; hf < NH; ++hf)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            const int tok = ts + 32 * hf + 16 * (e >> 3) + 8 * h2 + (e & 7);
+            const int tok = ts + 32 * (ks + hf) + 16 * (e >> 3) + 8 * h2 + (e & 7);
             if (tok > qpos) s[hf][e] = PS_NEG_INF;
           }
       }
       // max16 starts with the wait states an MFMA result needs before a vector instruction may read it
-      float tmax = max2(max16<true>(s[0]), max16<false>(s[1]));
+      float tmax = max16<true>(s[0]);
+      if (NH == 2) tmax = max2(tmax, max16<false>(s[NH - 1]));
       tmax = xor32_max(tmax) * P.scale_log2;
       // a row that sees nothing in this tile keeps its m; a row that has seen nothing yet in this
       // partition has m = -inf, l = 0 and all-zero accumulators
@@ -818,7 +836,7 @@ __device__ __forceinline__ void prefill_role(const StepParams& P, int bid, int H
       }
       const float m_use = m == PS_NEG_INF ? 0.f : m;  // all scores of such a row are -inf: exp2 gives 0
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
+      for (int hf = 0; hf < NH; ++hf) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[hf][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[hf][e], P.scale_log2, -m_use));
         uint4 pv[2];
@@ -842,6 +860,29 @@ __device__ __forceinline__ void prefill_role(const StepParams& P, int bid, int H
   __builtin_amdgcn_s_waitcnt(PS_VMCNT(0));  // no load may still be writing LDS when the wave ends
   if (bid < kClockSlots) clock_record(P, kClockSlots + bid, 2);
 
+  if (KS == 2) {  // the upper four waves hand their rows to the lower four, through the ring
+    float (*meet)[66][64] = (float (*)[66][64])sm;
+    __syncthreads();
+    if (ks == 1) {
+#pragma unroll
+      for (int n = 0; n < 4; ++n)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) meet[wrow][16 * n + e][lane] = acc[n][e];
+      meet[wrow][64][lane] = m;
+      meet[wrow][65][lane] = l;
+    }
+    __syncthreads();
+    if (ks == 1) return;
+    const float m1 = meet[wrow][64][lane], ms = fmaxf(m, m1);
+    // a wave that saw no key has m = -inf, l = 0 and zero accumulators
+    const float f0 = m == PS_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(m - ms), f1 = m1 == PS_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(m1 - ms);
+    l = l * f0 + meet[wrow][65][lane] * f1;
+    m = ms;
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[n][e] = acc[n][e] * f0 + meet[wrow][16 * n + e][lane] * f1;
+  }
   if (!active) return;
   const float ls = l + __shfl_xor(l, 32);
   const int row = q0 + j;
@@ -864,7 +905,7 @@ __device__ __forceinline__ void prefill_role(const StepParams& P, int bid, int H
         }
       }
   } else {  // one of several KV partitions of this row: unnormalised partial for the merge kernel
-    const int slot = t.part + (row - t.q0) * t.n_parts + t.k;
+    const int slot = t.part + (row - q_item) * t.n_parts + t.k;
     float* dst = P.partials + ((size_t)slot * P.Hq + head) * kPartStride;
 #pragma unroll
     for (int n = 0; n < 4; ++n)
@@ -890,6 +931,7 @@ __device__ __forceinline__ void prefill_role(const StepParams& P, int bid, int H
 // the two take 5 to 18 % less time than one after the other.  n_decode_wgs is a multiple of the
 // XCD count (padded with workgroups that exit at once), so that the prefill workgroups keep their
 // kv-head to XCD mapping.
+template <int KS>
 __global__ __launch_bounds__(kPrefillWaves * 64) void attention_kernel(StepParams P, const DecodeItem* __restrict__ ditems,
                                                                        const int32_t* __restrict__ dslots,
                                                                        const int32_t* __restrict__ block_ids, int n_slots,
@@ -904,7 +946,7 @@ __global__ __launch_bounds__(kPrefillWaves * 64) void attention_kernel(StepParam
   if ((int)blockIdx.x < n_decode_wgs)
     decode_role(P, ditems, dslots, block_ids, n_slots, blockIdx.x, (DecodeQ*)lds);
   else
-    prefill_role(P, (int)blockIdx.x - n_decode_wgs, HW, n_zsplit, (PrefillStage*)lds,
+    prefill_role<KS>(P, (int)blockIdx.x - n_decode_wgs, HW, n_zsplit, (PrefillStage*)lds,
                  (int*)(lds + sizeof(PrefillStage) * kStages));
 }
 
@@ -978,11 +1020,12 @@ int prefill_tile_tokens(int G) { return (kPrefillWaves / prefill_heads_per_wg(G)
 
 int decode_waves_per_wg() { return kDecodeWaves; }
 
-hipError_t launch_attention(const StepParams& p, int n_slots, int n_tiles, hipStream_t s, int* n_decode_wgs_out,
+hipError_t launch_attention(const StepParams& p, int n_slots, int n_tiles, int ks, hipStream_t s, int* n_decode_wgs_out,
                             int* n_prefill_wgs_out) {
   const int HW = prefill_heads_per_wg(p.G);
   const int nz = p.G / HW;
-  const long long n_prefill_wgs = (long long)n_tiles * p.Hkv * nz;
+  if (ks != 1 && ks != 2) return hipErrorInvalidValue;
+  const long long n_prefill_wgs = (long long)n_tiles * p.Hkv * nz * ks;
   // decode workgroups: one per kDecodeWaves slots and kv-head, rounded up to a multiple of 8 (XCDs)
   const long long n_decode_wgs = n_slots > 0 ? (((long long)(n_slots + kDecodeWaves - 1) / kDecodeWaves * p.Hkv + 7) / 8 * 8) : 0;
   const long long grid = n_decode_wgs + n_prefill_wgs;
@@ -990,8 +1033,12 @@ hipError_t launch_attention(const StepParams& p, int n_slots, int n_tiles, hipSt
   if (n_prefill_wgs_out) *n_prefill_wgs_out = (int)std::min<long long>(n_prefill_wgs, 0x7fffffffLL);
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attention_kernel, dim3((unsigned)grid), dim3(kPrefillWaves * 64), 0, s, p, p.ditems, p.dslots, p.block_ids,
-                     n_slots, (int)n_decode_wgs, HW, nz);
+  if (ks == 2)
+    hipLaunchKernelGGL(attention_kernel<2>, dim3((unsigned)grid), dim3(kPrefillWaves * 64), 0, s, p, p.ditems, p.dslots, p.block_ids,
+                       n_slots, (int)n_decode_wgs, HW, nz);
+  else
+    hipLaunchKernelGGL(attention_kernel<1>, dim3((unsigned)grid), dim3(kPrefillWaves * 64), 0, s, p, p.ditems, p.dslots, p.block_ids,
+                       n_slots, (int)n_decode_wgs, HW, nz);
   return hipGetLastError();
 }
 

@@ -10,6 +10,7 @@ alive and on the right device) or as integer addresses.  Batch arrays are numpy 
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
 import struct
 from typing import Optional, Tuple
@@ -369,7 +370,7 @@ def ps_sched_simulate(cfg: dict, dev_free_order, host_free_order, trace, max_ste
     d, h = _i32(dev_free_order), _i32(host_free_order)
     rec = np.zeros(max(len(trace), 1), dtype=_TRACE_DTYPE)   # column by column: a tenth of the time of one struct per request
     for name in ("rid", "arrival_ps", "prio", "prompt_len", "out_len"):
-        rec[name][:len(trace)] = [getattr(p, name) for p in trace]
+        rec[name][:len(trace)] = list(map(operator.attrgetter(name), trace))
     tr = rec.ctypes.data_as(C.POINTER(ps_trace_req))
     offs = np.zeros(len(trace) + 1, dtype=np.int64)
     np.cumsum(rec["out_len"][:len(trace)], out=offs[1:])

@@ -22,24 +22,30 @@ typedef __int128 i128;
 
 int sched_fail(int code, const char* fmt, ...);
 
-struct Req {
-  int64_t rid, arrival;
-  int32_t prio, prompt_len, out_len;
-  int32_t tag = -1;       // the caller's index of the request (ps_sched_simulate), not used by the rounds
+// A round walks all requests several times, and a queue of a hundred is 20 KB: what the walks read of every request is
+// its first cache line.
+struct alignas(64) Req {
+  int64_t arrival, last_sched;
   int64_t computed = 0;   // tokens whose KV exists (on the device, or on the host if evicted)
-  int64_t generated = 0;  // output tokens delivered
-  int64_t last_sched = 0;
+  int64_t exec = 0;       // of this round
+  int32_t prompt_len, out_len;
+  int32_t generated = 0;  // output tokens delivered
+  int32_t n_dev = 0, n_host = 0;  // sizes of dev_blocks and host_slots
+  int32_t tag = -1;       // the caller's index of the request (ps_sched_simulate), not used by the rounds
+  uint8_t prio;
+  bool decoding = false, urgent = false, in_batch = false, evicted_now = false;  // of this round
+  // the second line
+  alignas(64) int64_t rid;
+  int64_t weight = 0;     // of this round
   std::vector<int32_t> dev_blocks;  // logical order
   std::vector<int32_t> host_slots;  // host copies of logical blocks 0..n-1 (issued, maybe still in flight)
-  std::vector<int64_t> host_round;  // the scheduling round that issued each of them
-  // per-round scratch
-  int64_t exec = 0, remain = 0, weight = 0;
-  bool decoding = false, urgent = false, starving = false, in_batch = false, evicted_now = false, done = false;
+  std::vector<std::pair<int64_t, int32_t>> host_rounds;  // the scheduling rounds that issued them, oldest first: (round, copies up to and with it)
 
   int64_t need() const { return (int64_t)prompt_len + generated; }
-  int64_t b_miss() const {  // max(0, b_host - b_device)
-    const int64_t d = (int64_t)host_slots.size() - (int64_t)dev_blocks.size();
-    return d > 0 ? d : 0;
+  int64_t b_miss() const { return std::max(0, n_host - n_dev); }
+  void count() {
+    n_dev = (int32_t)dev_blocks.size();
+    n_host = (int32_t)host_slots.size();
   }
 };
 
@@ -48,10 +54,12 @@ struct Req {
 // One entry of the queue while it is being ordered: the sort key of its request next to it, so that a comparison reads
 // nothing but the two entries (except where two densities are too close for doubles).
 struct OrderKey {
-  int32_t group;  // 0 starving, 1 URGENT, 2 NORMAL, 3 arrival order only
-  double density; // group 1: weight / exec, rounded
-  int64_t k;      // group 0: time last scheduled; group 2: remaining time
   Req* r;
+  union {
+    double density;  // group 1: weight / exec, rounded
+    int64_t k;       // group 0: time last scheduled; group 2: remaining time
+  };
+  int32_t group;     // 0 starving, 1 URGENT, 2 NORMAL, 3 arrival order only
 };
 
 struct ps_sched {
@@ -59,8 +67,9 @@ struct ps_sched {
   std::vector<int32_t> dev_free, host_free;  // LIFO: back() is handed out next
   std::unordered_map<int64_t, Req*> by_id;
   std::vector<Req*> reqs;  // active requests, in the order of the last round, new ones behind
-  std::vector<OrderKey> keys;                        // scratch of a round
-  std::vector<Req*> Q;
+  std::vector<OrderKey> keys, moved;                 // scratch of a round
+  std::vector<Req*> later, offload;                  // not arrived; with enough blocks to offload
+  std::vector<size_t> ended;                         // places in the queue of the requests that are through with their output
   std::vector<std::pair<Req*, int64_t>> members;
   int64_t round = 0;        // ps_form_batch calls so far
   int64_t done_upto = 0;    // offloads issued in rounds <= this have completed (ps_sched_offloads_done)
@@ -112,6 +121,16 @@ int64_t copy_budget(const ps_sched_cfg& c, int64_t t_budget, int64_t t_fwd_min, 
   return lo;
 }
 
+// Hands out n blocks of a free list, last freed first, behind those `to` has.
+void take(std::vector<int32_t>& from, size_t n, std::vector<int32_t>& to) {
+  const size_t had = to.size();
+  to.resize(had + n);
+  const int32_t* src = from.data() + from.size();
+  int32_t* dst = to.data() + had;
+  for (size_t i = 0; i < n; ++i) dst[i] = src[-1 - (ptrdiff_t)i];
+  from.resize(from.size() - n);
+}
+
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Alg. 1 line 13 and the starvation rule: starving (longest wait first), URGENT by density descending, NORMAL by
@@ -132,21 +151,42 @@ bool before(const OrderKey& a, const OrderKey& b) {
 }
 
 // Sorts the queue, which comes in the order of the round before with new requests behind: from one round to the next few
-// requests change places, so an insertion sort is little more than a pass over the keys.  A request that moves usually
-// moves far (its group changes): its place is found by bisection and the keys in between move as one run.  When more than
-// a third of the requests have moved, a full sort takes over.
-void order_queue(std::vector<OrderKey>& keys) {
-  size_t moves_left = keys.size() / 3 + 16;
-  for (size_t i = 1; i < keys.size(); ++i) {
-    if (!before(keys[i], keys[i - 1])) continue;
-    if (moves_left-- == 0) {
+// requests change places.  Those that stand out of order are taken out (the larger one of a pair if it alone disturbs the
+// order, the smaller one otherwise), the rest closes up, and the sorted few go back from the largest down, each to the
+// place that bisection finds: every key moves twice at most, however far they go.  When more than a third of the requests
+// have moved, a full sort takes over.
+void order_queue(std::vector<OrderKey>& keys, std::vector<OrderKey>& moved) {
+  const size_t n = keys.size();
+  const size_t most = n / 3 + 16;
+  moved.clear();
+  OrderKey* const kept = keys.data();
+  size_t w = n > 0 ? 1 : 0;
+  for (size_t i = 1; i < n; ++i) {
+    const OrderKey x = keys[i];
+    if (!before(x, kept[w - 1])) {
+      kept[w++] = x;
+      continue;
+    }
+    if (moved.size() == most) {  // the keys in [w, i) have been copied: to the front, or to the list
+      std::copy(moved.begin(), moved.end(), kept + w);
       std::sort(keys.begin(), keys.end(), before);
       return;
     }
-    const OrderKey x = keys[i];
-    const auto at = std::upper_bound(keys.begin(), keys.begin() + (ptrdiff_t)i, x, before);
-    std::move_backward(at, keys.begin() + (ptrdiff_t)i, keys.begin() + (ptrdiff_t)i + 1);
-    *at = x;
+    if (i + 1 < n && before(keys[i + 1], kept[w - 1]) && (w == 1 || !before(x, kept[w - 2]))) {
+      moved.push_back(kept[w - 1]);
+      kept[w - 1] = x;
+    } else {
+      moved.push_back(x);
+    }
+  }
+  std::sort(moved.begin(), moved.end(), before);
+  size_t to = n;
+  for (size_t m = moved.size(); m-- > 0;) {
+    OrderKey* const at = std::upper_bound(kept, kept + w, moved[m], before);
+    std::move_backward(at, kept + w, kept + to);
+    to -= (size_t)(kept + w - at) + 1;
+    w = (size_t)(at - kept);
+    kept[to] = moved[m];
   }
 }
 
@@ -236,10 +276,13 @@ int ps_sched_add_request(ps_sched* s, int64_t rid, int64_t arrival_ps, int32_t p
   if (!r) return sched_fail(PS_ENOMEM, "out of host memory");
   r->rid = rid;
   r->arrival = arrival_ps;
-  r->prio = prio;
+  r->prio = (uint8_t)prio;
   r->prompt_len = prompt_len;
   r->out_len = out_len;
   r->last_sched = arrival_ps;  // "waiting time" counts from arrival until first scheduled
+  const size_t blocks = (size_t)std::min<int64_t>(ceil_div((int64_t)prompt_len + out_len, s->cfg.block_tokens), 4096);
+  r->dev_blocks.reserve(blocks);
+  r->host_slots.reserve(blocks);
   s->reqs.push_back(r);
   s->by_id[rid] = r;
   return PS_OK;
@@ -274,84 +317,115 @@ static int form_round(ps_sched* s, int64_t now, bool want_batch, ps_batch_out* o
   s->prio.clear();
   std::memset(out, 0, sizeof *out);
 
-  // queue = requests that have arrived
-  std::vector<Req*>& Q = s->Q;
-  Q.clear();
-  for (Req* r : s->reqs)
-    if (r->arrival <= now) Q.push_back(r);
-
+  // the queue: requests that have arrived, in the order of the round before; Alg. 1 lines 1-6: exec, remain, t_min
+  std::vector<OrderKey>& keys = s->keys;
+  keys.clear();
+  s->later.clear();
   int64_t t_budget = 0, phi = 0, b_copy = 0, t_batch = 0;
+  int64_t t_min = INT64_MAX, sum_exec = 0, b_missing = 0;
+  const size_t n_active = s->reqs.size();
+  for (size_t i = 0; i < n_active; ++i) {
+    Req* const r = s->reqs[i];
+    __builtin_prefetch(s->reqs[std::min(i + 12, n_active - 1)]);
+    if (r->arrival > now) {
+      s->later.push_back(r);
+      continue;
+    }
+    const int64_t lq = r->need() - r->computed, generated = r->generated;
+    const bool dec = generated >= 1 && lq == 1;
+    r->decoding = dec && r->n_host <= r->n_dev;  // and nothing of it is on the host only
+    r->exec = dec ? t_decode(c, r->need()) : t_prefill(c, lq, r->computed);
+    r->in_batch = r->evicted_now = false;
+    OrderKey k;
+    k.k = c.ttft_slo_ps + generated * c.tpot_slo_ps - (now - r->arrival);  // remain: time left to the next token's deadline
+    k.r = r;
+    keys.push_back(k);
+    t_min = std::min(t_min, k.k);
+    sum_exec += r->exec;
+    b_missing += r->b_miss();
+  }
   std::vector<std::pair<Req*, int64_t>>& members = s->members;
   members.clear();
-  if (!Q.empty()) {
-    // Alg. 1 lines 1-6: exec, remain, density (as weight / exec), t_min
-    int64_t t_min = INT64_MAX, sum_exec = 0, b_missing = 0;
-    for (Req* r : Q) {
-      const int64_t lq = r->need() - r->computed;
-      const bool dec = r->generated >= 1 && lq == 1;
-      r->decoding = dec && r->host_slots.size() <= r->dev_blocks.size();  // and nothing of it is on the host only
-      r->exec = dec ? t_decode(c, r->need()) : t_prefill(c, lq, r->computed);
-      const int64_t i = r->generated + 1;  // index of the next token to deliver
-      r->remain = c.ttft_slo_ps + (i - 1) * c.tpot_slo_ps - (now - r->arrival);
-      r->weight = (i == 1 ? c.w_first : c.w_decode) * c.class_weight[r->prio - 1];
-      r->in_batch = r->evicted_now = false;
-      t_min = std::min(t_min, r->remain);
-      sum_exec += r->exec;
-      b_missing += r->b_miss();
-    }
+  s->offload.clear();
+  s->ended.clear();
+  size_t n_emitted = 0, n_members = 0;
+  if (!keys.empty()) {
     // line 7
     t_budget = std::max(t_min, c.eta_ps);
     // Eq. 8 and lines 8-12
     phi = (int64_t)(((i128)t_budget * sum_exec) / (t_budget - c.t_c));
-    for (Req* r : Q) {
-      r->urgent = (i128)r->remain * c.gamma_den < (i128)c.gamma_num * phi;
-      r->starving = now - r->last_sched > c.tau_ps;
-    }
-    // line 13 and the starvation rule (see before())
+    // lines 8-13 and the starvation rule (see before())
     const bool fcfs = c.order_policy == PS_ORDER_FCFS;  // comparison arm: arrival order, nothing else
-    std::vector<OrderKey>& keys = s->keys;
-    keys.clear();
-    for (Req* r : Q) {
-      OrderKey k;
-      k.group = fcfs ? 3 : (r->starving ? 0 : (r->urgent ? 1 : 2));
-      k.density = k.group == 1 ? (double)r->weight / (double)std::max<int64_t>(r->exec, 1) : 0.0;
-      k.k = k.group == 0 ? r->last_sched : (k.group == 2 ? r->remain : 0);
-      k.r = r;
-      keys.push_back(k);
-    }
-    order_queue(keys);
-    for (size_t i = 0; i < Q.size(); ++i) Q[i] = keys[i].r;
-    {  // the active requests take over this order; those that have not arrived yet follow
-      size_t w = Q.size();
-      if (w != s->reqs.size()) {
-        std::vector<Req*> later;
-        for (Req* r : s->reqs)
-          if (r->arrival > now) later.push_back(r);
-        std::copy(later.begin(), later.end(), s->reqs.begin() + (ptrdiff_t)w);
+    const i128 urgent_below = (i128)c.gamma_num * phi;
+    for (OrderKey& k : keys) {
+      Req* r = k.r;
+      r->urgent = (i128)k.k * c.gamma_den < urgent_below;
+      const bool starving = now - r->last_sched > c.tau_ps;
+      if (fcfs) {
+        k.group = 3;
+        k.k = 0;
+      } else if (starving) {
+        k.group = 0;
+        k.k = r->last_sched;
+      } else if (r->urgent) {  // density: weight / exec
+        k.group = 1;
+        r->weight = (r->generated == 0 ? c.w_first : c.w_decode) * c.class_weight[r->prio - 1];
+        k.density = (double)r->weight / (double)std::max<int64_t>(r->exec, 1);
+      } else {
+        k.group = 2;
       }
-      std::copy(Q.begin(), Q.end(), s->reqs.begin());
     }
+    order_queue(keys, s->moved);
+    // the active requests take over this order; those that have not arrived yet follow
+    for (size_t i = 0; i < keys.size(); ++i) s->reqs[i] = keys[i].r;
+    std::copy(s->later.begin(), s->later.end(), s->reqs.begin() + (ptrdiff_t)keys.size());
+    Req* const* Q = s->reqs.data();
+    const size_t n_queue = keys.size();
     if (want_batch)
-      for (Req* r : Q) {
-        s->order.push_back(r->rid);
-        if (r->urgent) s->urgent.push_back(r->rid);
+      for (size_t i = 0; i < n_queue; ++i) {
+        s->order.push_back(Q[i]->rid);
+        if (Q[i]->urgent) s->urgent.push_back(Q[i]->rid);
       }
+    size_t idx = 0;
+    // what a member's turn ends with: its token, if it has computed everything before it, is delivered when the batch ends;
+    // blocks are given back and copied once the batch stands
+    members.resize(n_queue);
+    s->emitted_req.resize(n_queue);
+    s->emitted_index.resize(n_queue);
+    auto* const to_members = members.data();
+    int64_t* const to_req = s->emitted_req.data();
+    int32_t* const to_index = s->emitted_index.data();
+    int64_t n_off[8];  // full blocks without a host copy that start an offload, by class
+    for (int p = 0; p < 8; ++p) n_off[p] = std::max<int64_t>(1, (int64_t)c.n_off_base >> p);
+    const auto admitted = [&](Req* r, int64_t chunk) {
+      r->computed += chunk;
+      r->last_sched = now;
+      r->in_batch = true;
+      to_members[n_members].first = r;
+      to_members[n_members++].second = chunk;
+      if (r->computed == r->need()) {
+        r->generated += 1;
+        to_req[n_emitted] = want_batch ? r->rid : r->tag;
+        to_index[n_emitted++] = r->generated;
+        if (r->generated == r->out_len) {
+          s->ended.push_back(idx - 1);
+          return;
+        }
+      }
+      if (r->computed >= (r->n_host + n_off[r->prio - 1]) * blk) s->offload.push_back(r);
+    };
     // line 14
     b_copy = copy_budget(c, t_budget, c.t_c + sum_exec, b_missing);
     int64_t b_rem = b_copy;
     // lines 15-23
     t_batch = c.t_c;
-    size_t idx = 0;
-    size_t tail = Q.size();  // requests from here on have been looked at as victims: none becomes one later in the round
-    while (idx < Q.size() && t_batch < t_budget) {
+    size_t tail = n_queue;  // requests from here on have been looked at as victims: none becomes one later in the round
+    while (idx < n_queue && t_batch < t_budget) {
       Req* r = Q[idx++];
       if (r->evicted_now) continue;
-      if (r->decoding && r->need() <= (int64_t)r->dev_blocks.size() * blk) {  // a decode token that needs no block: most of a round
-        r->computed += 1;
-        r->last_sched = now;
-        r->in_batch = true;
+      if (r->decoding && r->need() <= r->n_dev * blk) {  // a decode token that needs no block: most of a round
         t_batch += r->exec;
-        members.emplace_back(r, 1);
+        admitted(r, 1);
         continue;
       }
       const int64_t T = t_budget - t_batch;
@@ -377,7 +451,7 @@ static int form_round(ps_sched* s, int64_t now, bool want_batch, ps_batch_out* o
         const bool ok = chunk == lq || (i128)chunk * c.beta_den > (i128)c.beta_num * (miss - k) * blk;
         if (!ok) continue;
       }
-      const int64_t held = (int64_t)r->dev_blocks.size();
+      const int64_t held = r->n_dev;
       int64_t want = ceil_div(comp + chunk, blk) - held;
       if (want > (int64_t)s->dev_free.size()) {
         // victims from the tail of the sorted queue, behind r, never a near-starved request
@@ -389,10 +463,11 @@ static int form_round(ps_sched* s, int64_t now, bool want_batch, ps_batch_out* o
           v->dev_blocks.clear();
           // host copies still in flight are discarded with the eviction (Sec. 4.3, Asynchronous
           // Offloading): only completed ones keep their tokens from being recomputed
-          const size_t conf = (size_t)(std::upper_bound(v->host_round.begin(), v->host_round.end(), s->done_upto) - v->host_round.begin());
+          while (!v->host_rounds.empty() && v->host_rounds.back().first > s->done_upto) v->host_rounds.pop_back();
+          const size_t conf = v->host_rounds.empty() ? 0 : (size_t)v->host_rounds.back().second;
           s->host_free.insert(s->host_free.end(), v->host_slots.begin() + (ptrdiff_t)conf, v->host_slots.end());
           v->host_slots.resize(conf);
-          v->host_round.resize(conf);
+          v->count();
           v->computed = std::min<int64_t>(v->computed, (int64_t)conf * blk);
           v->evicted_now = true;
           s->evicted.push_back(v->rid);
@@ -407,29 +482,28 @@ static int form_round(ps_sched* s, int64_t now, bool want_batch, ps_batch_out* o
       }
       // admit
       if (miss > 0) {
-        r->dev_blocks.assign(s->dev_free.rbegin(), s->dev_free.rbegin() + (ptrdiff_t)k);
-        s->dev_free.resize(s->dev_free.size() - (size_t)k);
+        r->dev_blocks.clear();
+        take(s->dev_free, (size_t)k, r->dev_blocks);
         if (want_batch) {
           s->si_host.insert(s->si_host.end(), r->host_slots.begin(), r->host_slots.begin() + (ptrdiff_t)k);
           s->si_dev.insert(s->si_dev.end(), r->dev_blocks.begin(), r->dev_blocks.end());
         }
         s->host_free.insert(s->host_free.end(), r->host_slots.begin() + (ptrdiff_t)k, r->host_slots.end());
         r->host_slots.resize((size_t)k);
-        r->host_round.resize((size_t)k);
+        while (r->host_rounds.size() > 1 && r->host_rounds[r->host_rounds.size() - 2].second >= k) r->host_rounds.pop_back();
+        if (!r->host_rounds.empty()) r->host_rounds.back().second = (int32_t)k;  // k is less than all copies, or all of them
         r->computed = comp;
         b_rem -= k;
         want -= k;
       }
-      if (want > 0) {
-        r->dev_blocks.insert(r->dev_blocks.end(), s->dev_free.rbegin(), s->dev_free.rbegin() + (ptrdiff_t)want);
-        s->dev_free.resize(s->dev_free.size() - (size_t)want);
-      }
-      r->computed += chunk;
-      r->last_sched = now;
-      r->in_batch = true;
+      if (want > 0) take(s->dev_free, (size_t)want, r->dev_blocks);
+      r->count();
       t_batch += t;
-      members.emplace_back(r, chunk);
+      admitted(r, chunk);
     }
+    members.resize(n_members);
+    s->emitted_req.resize(n_emitted);
+    s->emitted_index.resize(n_emitted);
     if (members.empty()) t_batch = 0;
   }
 
@@ -447,54 +521,38 @@ static int form_round(ps_sched* s, int64_t now, bool want_batch, ps_batch_out* o
       s->bt_start.push_back((int32_t)s->block_ids.size());
       s->prio.push_back((uint8_t)r->prio);
     }
-  // token delivery at now + T_pd(B), completion
-  for (auto& mc : members) {
-    Req* r = mc.first;
-    if (r->computed != r->need()) continue;
-    r->generated += 1;
-    s->emitted_req.push_back(want_batch ? r->rid : r->tag);
-    s->emitted_index.push_back((int32_t)r->generated);
-    if (r->generated == r->out_len) {
-      r->done = true;
-      s->dev_free.insert(s->dev_free.end(), r->dev_blocks.begin(), r->dev_blocks.end());
-      s->host_free.insert(s->host_free.end(), r->host_slots.begin(), r->host_slots.end());
-      r->dev_blocks.clear();
-      r->host_slots.clear();
-      r->host_round.clear();
-      s->finished.push_back(want_batch ? r->rid : r->tag);
-    }
+  // completion
+  for (size_t at : s->ended) {
+    Req* r = s->reqs[at];
+    s->dev_free.insert(s->dev_free.end(), r->dev_blocks.begin(), r->dev_blocks.end());
+    s->host_free.insert(s->host_free.end(), r->host_slots.begin(), r->host_slots.end());
+    s->finished.push_back(want_batch ? r->rid : r->tag);
   }
   // asynchronous offload: every n_off^r newly completed full blocks of r get a host copy
   int32_t n_offloaded = 0;
-  for (auto& mc : members) {
-    Req* r = mc.first;
-    if (r->done) continue;
-    int64_t n_off = (int64_t)c.n_off_base >> (r->prio - 1);
-    if (n_off < 1) n_off = 1;
-    const int64_t copied = (int64_t)r->host_slots.size();
-    if (r->computed < (copied + n_off) * blk) continue;  // fewer than n_off full blocks without a host copy
+  for (Req* r : s->offload) {
+    const int64_t copied = r->n_host;
     const int64_t pending = r->computed / blk - copied;
     if ((int64_t)s->host_free.size() < pending) continue;
-    r->host_slots.insert(r->host_slots.end(), s->host_free.rbegin(), s->host_free.rbegin() + (ptrdiff_t)pending);
-    s->host_free.resize(s->host_free.size() - (size_t)pending);
-    r->host_round.insert(r->host_round.end(), (size_t)pending, s->round);
+    take(s->host_free, (size_t)pending, r->host_slots);
+    r->count();
+    r->host_rounds.emplace_back(s->round, r->n_host);
     n_offloaded += (int32_t)pending;
     if (want_batch) {
       s->so_dev.insert(s->so_dev.end(), r->dev_blocks.begin() + (ptrdiff_t)copied, r->dev_blocks.begin() + (ptrdiff_t)(copied + pending));
       s->so_host.insert(s->so_host.end(), r->host_slots.end() - (ptrdiff_t)pending, r->host_slots.end());
     }
   }
-  if (!s->finished.empty()) {
-    size_t w = 0;
-    for (Req* r : s->reqs) {
-      if (!r->done) {
-        s->reqs[w++] = r;
-        continue;
-      }
+  if (!s->ended.empty()) {  // the others close up
+    auto w = s->reqs.begin() + (ptrdiff_t)s->ended[0];
+    for (size_t i = 0; i < s->ended.size(); ++i) {
+      Req* r = s->reqs[s->ended[i]];
+      const auto next = i + 1 < s->ended.size() ? s->reqs.begin() + (ptrdiff_t)s->ended[i + 1] : s->reqs.end();
+      w = std::copy(s->reqs.begin() + (ptrdiff_t)s->ended[i] + 1, next, w);
       s->by_id.erase(r->rid);
       delete r;
     }
-    s->reqs.resize(w);
+    s->reqs.resize(s->reqs.size() - s->ended.size());
   }
 
   out->batch.n_req = (int32_t)members.size();
@@ -568,7 +626,11 @@ int ps_sched_simulate(const ps_sched_cfg* cfg, const int32_t* dev_free_order, in
   ps_sched* s = nullptr;
   int rc = ps_sched_create(cfg, dev_free_order, n_dev, host_free_order, n_host, &s);
   if (rc != PS_OK) return rc;
-  // arrival order (ties by id); where each request's token times go
+  // arrival order (ties by id); where each request's token times go, and its arrival beside that
+  struct Deliver {
+    int64_t* to;
+    int64_t arrival;
+  };
   std::vector<int32_t> by_arrival((size_t)n_trace);
   std::vector<int64_t> t_off((size_t)n_trace + 1, 0);
   std::unordered_set<int64_t> ids;
@@ -595,7 +657,10 @@ int ps_sched_simulate(const ps_sched_cfg* cfg, const int32_t* dev_free_order, in
     own_counts.assign((size_t)n_trace, 0);
     n_delivered = own_counts.data();
   }
-  for (int32_t i = 0; i < n_trace; ++i) n_delivered[i] = 0;
+  std::vector<Deliver> deliver((size_t)n_trace);
+  for (int32_t i = 0; i < n_trace; ++i) deliver[(size_t)i] = Deliver{token_times + t_off[(size_t)i], trace[i].arrival_ps};
+  std::fill(n_delivered, n_delivered + n_trace, 0);
+  const auto count = [&](int32_t i) { return n_delivered[i] = (int32_t)(deliver[(size_t)i].to - (token_times + t_off[(size_t)i])); };
   // the offload thread on the same clock: a round's copies start when its batch has been computed and
   // the earlier copies are through, and take t_block per block
   std::vector<std::pair<int64_t, int64_t>> inflight;  // (round, completion time), oldest first
@@ -628,15 +693,15 @@ int ps_sched_simulate(const ps_sched_cfg* cfg, const int32_t* dev_free_order, in
       inflight.emplace_back(fb.round, copy_free_at);
     }
     for (int32_t e = 0; e < fb.n_emitted; ++e) {  // tokens are delivered when the batch ends
-      const int32_t i = (int32_t)fb.emitted_req[e];
-      token_times[t_off[(size_t)i] + n_delivered[i]] = now + fb.t_batch_ps - trace[i].arrival_ps;
-      n_delivered[i] += 1;
+      if (e + 12 < fb.n_emitted) __builtin_prefetch(deliver[(size_t)fb.emitted_req[e + 12]].to, 1);
+      Deliver& d = deliver[(size_t)fb.emitted_req[e]];
+      *d.to++ = now + fb.t_batch_ps - d.arrival;
     }
     for (int32_t f = 0; f < fb.n_finished; ++f) {
       const int32_t i = (int32_t)fb.finished[f];
       int64_t g = 0, ideal = 0;
       int32_t ok = 0;
-      (void)ps_tdg_score(cfg, trace[i].prio, trace[i].out_len, token_times + t_off[(size_t)i], n_delivered[i], &g, &ideal, &ok);
+      (void)ps_tdg_score(cfg, trace[i].prio, trace[i].out_len, token_times + t_off[(size_t)i], count(i), &g, &ideal, &ok);
       out->gain += g;
       out->ideal_gain += ideal;
       out->slo_attained += ok;
@@ -644,6 +709,7 @@ int ps_sched_simulate(const ps_sched_cfg* cfg, const int32_t* dev_free_order, in
     }
     now += fb.t_batch_ps > 0 ? fb.t_batch_ps : cfg->eta_ps;
   }
+  for (int32_t i = 0; i < n_trace; ++i) (void)count(i);
   out->steps = steps;
   out->end_ps = now;
   ps_sched_destroy(s);

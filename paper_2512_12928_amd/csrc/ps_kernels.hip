@@ -327,7 +327,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int tile0 = n_tiles * wave / NW, tile1 = n_tiles * (wave + 1) / NW;  // this wave's tiles; may be none
   const int32_t* table = block_ids + it.bt_off;
 
-  float m = PS_NEG_INF, l = 0.f;
+  // finite: a wave may start on a tile of keys whose scores are all -inf (or have no tile), with l = 0 and acc = 0 until a
+  // key counts; the other waves' maxima then give it weight 0
+  float m = -__FLT_MAX__, l = 0.f;
   f32x4 acc[8];
 #pragma unroll
   for (int n = 0; n < 8; ++n) acc[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -405,7 +407,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int n = 0; n < 8; ++n) t.v[n] = zero_from8(t.v[n], ts + 8 * kg, it.t1);
       }
       tmax = xor32_max(xor16_max(tmax));
-      const float m_new = fmaxf(m, tmax);  // finite: every tile holds at least one valid token
+      const float m_new = fmaxf(m, tmax);
       const float alpha = __builtin_amdgcn_exp2f(m - m_new);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -467,7 +469,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float f = __builtin_amdgcn_exp2f(mw[w] - ms);  // 0 for a wave without tiles (m = -inf): ms is finite
+      const float f = __builtin_amdgcn_exp2f(mw[w] - ms);  // a wave without a key has l = 0 and o = 0
       L += part[w][h][129] * f;
       o += *(const f32x4*)&part[w][h][x] * f;
     }

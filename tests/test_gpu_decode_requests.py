@@ -73,3 +73,13 @@ def test_every_decode_path_appends(kw):
     items = [(1, L) for L in EDGES] + ([(40, 90), (70, 70)] if "mixed_launch" in kw else [])
     b, t = batch_of(8, 2, items, seed=88)
     check(b, t, **kw)
+
+
+@pytest.mark.parametrize("dead", [(0, 64), (32, 550), (0, 599)])
+def test_a_run_of_keys_without_weight(dead):
+    """Keys at minus infinity have weight 0, also where they are all that a wave, or a partition, has seen so far."""
+    b, t = batch_of(8, 2, [(1, 600)] * 3 + [(1, 1700)], seed=91)
+    t.q[:, :, 0] = 0x3F80                       # 1.0
+    for k in t.k:
+        k[dead[0]:dead[1], :, 0] = 0xFF80       # -inf
+    check(b, t)

@@ -241,6 +241,8 @@ int ps_plan_decode(const ps_layer_cfg* cfg, const ps_batch* batch, int32_t waves
  * decode units as those finish). For tests of that host logic.
  * A decode-only batch whose time is latency rather than bytes (few or short requests) is laid out by request: every
  * segment (a request, or one of the equal parts a long one is cut into) gets a workgroup of 4 or 8 waves per kv-head.
+ * (The answer is for a step with new rows; where one request's table names the block another one's row goes to, such a
+ * step keeps the slots.)
  *   out6[0] decode waves     out6[1] decode slots (waves / Hkv); laid out by request: segments, and workgroups
  *   out6[2] decode workgroups (four slots each; laid out by request, one segment each); 0 for a mixed batch whose workgroups carry both kinds of work (cfg.mixed_launch):
  *           then every prefill workgroup also walks up to two of the decode slots

@@ -83,6 +83,7 @@ struct DecodePlan {
   std::vector<ps::MergeItem> mitems;
   std::vector<int> scratch;
   std::vector<double> bins;
+  std::vector<uint8_t> is_tail;  // per device block, all 0 between calls (new_row_is_shared)
   std::vector<ps::RequestItem> ritems;  // what goes to the device in the place of ditems if request_waves > 0
   int longest_merge = 0;                // partitions of the merge item that has most
   int prefill_ks = 1;     // workgroups per prefill work item
@@ -435,6 +436,23 @@ void build_decode_slots(DecodePlan* c, int n_kv_heads, int decode_chunk, const p
   close_slot();
 }
 
+// Whether a request's table names the block that another one of them (or the same, elsewhere) appends this step's row to.
+// An append launch ahead of the attention shows that row to all of them; where the request's own workgroup writes it, nobody
+// else may read it.  One pass over the tables: 1 us per thousand blocks, for launches of at most 200 us.
+bool new_row_is_shared(DecodePlan* c, const ps_batch* b, const std::vector<int>& reqs, int n_blocks) {
+  if (c->is_tail.size() < (size_t)n_blocks) c->is_tail.resize((size_t)n_blocks, 0);
+  size_t tails = 0, named = 0;  // blocks that are somebody's tail, table entries that name one
+  for (int r : reqs) {
+    uint8_t& t = c->is_tail[(size_t)b->block_ids[b->bt_start[r + 1] - 1]];
+    tails += t == 0;
+    t = 1;
+  }
+  for (int r : reqs)
+    for (int i = b->bt_start[r]; i < b->bt_start[r + 1]; ++i) named += c->is_tail[(size_t)b->block_ids[i]];
+  for (int r : reqs) c->is_tail[(size_t)b->block_ids[b->bt_start[r + 1] - 1]] = 0;
+  return tails != reqs.size() || named != tails;
+}
+
 // Decode-only batches of few requests: should every segment get workgroups of its own (decode_request_kernel), and which
 // segments?  Priced, in us, from what the kernels take on an MI355X:
 //  - a launch whose workgroups walk next to nothing takes 4.2 (launch, item, first tile, one meeting in LDS), the slot
@@ -446,7 +464,7 @@ void build_decode_slots(DecodePlan* c, int n_kv_heads, int decode_chunk, const p
 // Candidates: workgroups of 8 waves (one per compute unit) or 4 (two per unit), requests whole or cut into equal segments
 // of at most `cap` tiles, from the shortest cap at which all segments run at once.
 bool build_decode_requests(DecodePlan* c, const ps_batch* b, const std::vector<int>& reqs, int& n_parts, int n_kv_heads, int n_cus,
-                           double stream_TBps) {
+                           double stream_TBps, int n_blocks, bool append) {
   constexpr double kLaunchUs = 4.2, kMergeUs = 3.0, kTileUs = 0.36, kAgainUs = 5.0, kStreamLoss = 1.08;
   constexpr double kSlotLaunchUs = 9.5, kSlotTileUs = 0.9, kSlotRequestUs = 2.0;
   const double tile_us = 4.0 * ps::kTileTokens * ps::kHeadDim / (stream_TBps * 1e6);  // of the whole chip's stream
@@ -519,7 +537,7 @@ bool build_decode_requests(DecodePlan* c, const ps_batch* b, const std::vector<i
       if (cp >= longest) break;
     }
   }
-  if (waves == 0) return false;
+  if (waves == 0 || (append && new_row_is_shared(c, b, reqs, n_blocks))) return false;
   c->ditems.clear();
   c->dslots.assign(1, 0);
   for (int r : reqs) {
@@ -1137,7 +1155,9 @@ static int plan_batch(ps_ctx* c, const ps_batch* b, bool has_new_kv, size_t work
       std::vector<int64_t> weight((size_t)per_item * tiles.size());
       for (size_t x = 0; x < weight.size(); ++x) weight[x] = tiles[x / (size_t)per_item].reach;
       build_weighted_decode_slots(&c->plan, b, decode_reqs, n_parts, weight);
-    } else if (c->cfg.decode_chunk == 0 && c->cfg.decode_waves == 0 && tiles.empty() && build_decode_requests(&c->plan, b, decode_reqs, n_parts, c->cfg.n_kv_heads, c->n_cus, tune.stream_TBps)) {
+    } else if (c->cfg.decode_chunk == 0 && c->cfg.decode_waves == 0 && tiles.empty() &&
+               build_decode_requests(&c->plan, b, decode_reqs, n_parts, c->cfg.n_kv_heads, c->n_cus, tune.stream_TBps,
+                                     c->cfg.n_device_blocks, has_new_kv)) {
       c->aitems.clear();  // the attention launch appends
     } else {
       build_decode_slots(&c->plan, c->cfg.n_kv_heads, c->cfg.decode_chunk, b, decode_reqs, n_parts, waves);
@@ -1496,7 +1516,7 @@ int ps_plan_launch(const ps_layer_cfg* cfg, const ps_batch* b, int32_t n_cus, in
   c.n_cus = n_cus;
   int n_parts = 0;
   int64_t split = 0;
-  int rc = plan_batch(&c, b, false, (size_t)1 << 62, decode_kv, n_parts, &split);
+  int rc = plan_batch(&c, b, true, (size_t)1 << 62, decode_kv, n_parts, &split);
   if (rc != PS_OK) return rc;
   const int n_slots = (int)c.plan.dslots.size() - 1;
   const int dw = ps::decode_waves_per_wg();

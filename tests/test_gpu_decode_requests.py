@@ -83,3 +83,22 @@ def test_a_run_of_keys_without_weight(dead):
     for k in t.k:
         k[dead[0]:dead[1], :, 0] = 0xFF80       # -inf
     check(b, t)
+
+
+def test_a_row_that_another_request_reads():
+    """The second request's context runs over the block that the first one's row completes in this step."""
+    b, t = batch_of(8, 2, [(1, 48), (1, 80), (1, 20)], seed=92)
+    b.block_ids[b.bt_start[1]:b.bt_start[1] + 3] = b.table(0)
+    for x in (t.k, t.v):
+        x[1][:48] = x[0]
+    full = oracle_cache(b, t)
+    want = A.paged_attention(t.q, full, b.q_start, b.kv_len, b.bt_start, b.block_ids)
+    start = oracle_cache(b, t, upto_prefix=True)
+    start.append(b.table(0)[2:], 15, *(np.full_like(x[0][:1], W.BF16_NAN) for x in (t.k, t.v)))
+    cache = u16_to_dev(to_device_layout(start.pool))
+    k_new, v_new = t.new_rows(b)
+    lay = Layer(b)
+    out = lay.step(b, u16_to_dev(t.q), cache, u16_to_dev(k_new), u16_to_dev(v_new))
+    lay.close()
+    check_close(out.cpu().numpy().astype(np.float64), want, False)
+    assert np.array_equal(from_device_layout(dev_to_u16(cache), 2), full.pool)

@@ -163,3 +163,19 @@ def test_planner_constants_move_the_share_and_the_split():
         with pytest.raises(B.PsError) as e:
             plan(b, **bad)
         assert e.value.code == B.PS_EINVAL
+
+
+@pytest.mark.parametrize("who, entry, whose", [(1, 0, 0), (0, 0, 0), (2, -1, 0), (0, 3, 2)])
+def test_a_row_that_another_request_reads_is_appended_ahead(who, entry, whose):
+    """Laid out by request, a step's row is written by the request's own workgroup; a table that names the block it goes to
+    (another request's, the same one's at another place, two requests with one last block) keeps the layout whose append
+    comes first."""
+    b = W.build_batch(W.LayerShape(32, 8), [(1, 80), (1, 33), (1, 16)], [1] * 3, np.random.default_rng(3), seed=3)
+    p = plan(b)
+    assert p["decode_slots"] == 3 and p["decode_workgroups"] == 24          # by request
+    t = b.bt_start[who + 1] - 1 if entry < 0 else b.bt_start[who] + entry
+    b.block_ids[t] = b.block_ids[b.bt_start[whose + 1] - 1]
+    q = plan(b)
+    assert q["decode_slots"] == 1 and q["decode_workgroups"] == 8           # five tiles in one slot of at least four
+    b.block_ids[t] = (set(range(b.n_device_blocks)) - set(b.block_ids.tolist())).pop()
+    assert plan(b) == p
